@@ -8,6 +8,7 @@
 #include <cstring>
 #include <new>
 
+#include "cells.hpp"
 #include "correct.hpp"
 #include "predict.hpp"
 #include "sym.hpp"
@@ -288,6 +289,7 @@ int tsbts_destroy(tsbts_ctx *c) {
   if (c->sym_items) (void)hipFree(c->sym_items);
   if (c->sym_part) (void)hipFree(c->sym_part);
   if (c->split_buf) (void)hipFree(c->split_buf);
+  if (c->cell_buf) (void)hipFree(c->cell_buf);
   if (c->idx_flag_h) (void)hipHostFree(c->idx_flag_h);
   dev_free(c->idx_seen);
   dev_free(c->done);
@@ -528,13 +530,17 @@ int tsbts_timestep(tsbts_ctx *c, const int32_t *idx, int32_t n_act, double eta, 
   if (!dtc) return fail(c, TSBTS_EINVAL, "dtc is NULL");
   if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, TSBTS_EINVAL, "eta must be > 0");
   if (!c->have_pred) return fail(c, TSBTS_ESTATE, "no predicted particle arrays");
-  if (int s = ensure_part(c, partial_elems_needed(c, n_act))) return s;
-  if (criterion_sym_applies(c, n_act)) {
-    const int vb = c->precision == TSBTS_FP64 ? 8 : 4;
-    if (int s = sym_prepare(c, 2, vb, vb))
-      return fail(c, s, "symmetric criterion: work list or partials not allocated");
+  // without the buffers of the spatial order the other kernels serve the call
+  if (!cells_criterion_applies(c, n_act) || !cells_prepare(c)) {
+    if (int s = ensure_part(c, partial_elems_needed(c, n_act))) return s;
+    if (criterion_sym_applies(c, n_act)) {
+      const int vb = c->precision == TSBTS_FP64 ? 8 : 4;
+      if (int s = sym_prepare(c, 2, vb, vb))
+        return fail(c, s, "symmetric criterion: work list or partials not allocated");
+    }
+    if (int s = split_prepare(c, n_act))
+      return fail(c, s, "split call: buffers not allocated");
   }
-  if (int s = split_prepare(c, n_act)) return fail(c, s, "split call: buffers not allocated");
   hipError_t e = launch_timestep(c, idx, n_act, eta, dtc, stream);
   if (e != hipSuccess) return hip_fail(c, e, "tsbts_timestep launch");
   return TSBTS_OK;

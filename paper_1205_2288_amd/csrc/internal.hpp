@@ -93,6 +93,9 @@ struct tsbts_ctx {
   void *split_buf = nullptr;
   int64_t split_cap = 0;
   int tune_split = 2;  // 0 off, 1 from kSplitMinAct targets, 2 automatic
+  // spatial order of the criterion of large active sets (timestep_cells.hip): one
+  // allocation for npad particles
+  void *cell_buf = nullptr;
   char err[512] = {0};
 };
 

@@ -9,6 +9,7 @@
 // in the tiles that hold some lane's own particle (wave-uniform vote), as in the force,
 // and so are the padding particles of the last tile (at rest far away they would add a
 // tiny nonzero v^2/r^2, which matters when every real relative velocity is zero).
+#include "cells.hpp"
 #include "criterion.hpp"
 #include "sym.hpp"
 
@@ -423,6 +424,10 @@ hipError_t run_precision(const tsbts_ctx *c, StepArgs &A, hipStream_t st) {
 
 hipError_t launch_timestep(tsbts_ctx *c, const int32_t *idx, int n_act, double eta,
                            double *dtc, hipStream_t st) {
+  if (cells_criterion_applies(c, n_act)) {
+    const hipError_t e = launch_timestep_cells(c, idx, n_act, eta, dtc, st);
+    if (e != hipErrorNotReady) return e;
+  }
   if (split_applies(c, n_act)) {
     const hipError_t e = launch_timestep_split(c, idx, n_act, eta, dtc, st);
     if (e != hipErrorNotReady) return e;
