@@ -274,28 +274,29 @@ __device__ __forceinline__ void small_tile_sums(const ForceArgs &A, const typena
     double s = 0.0;
 #pragma unroll
     for (int ww = 0; ww < kWG / 64; ++ww) s += static_cast<double>(red[q][c][ww]);
-    A.part[(static_cast<int64_t>(tile) * 4 + c) * A.n_act + q] = s;
+    store_partial(&A.part[(static_cast<int64_t>(tile) * 4 + c) * A.n_act + q], s);
   }
 }
 
 // The split-j reduction by the launch's last workgroup.  A slice's partials form a row of
-// W = 4 n_act values; thread t adds value t % W over part t / W of the slices (P = kWG / W
-// consecutive parts, coalesced rows), in slice order; the parts are then added in order
-// and each target finishes (sg: the active list in LDS; ts: the corrector's inputs of
-// target tid, held by thread tid, or null).
+// W = 4 n_act values; thread t adds value t % W over part t / W of the slices (at most
+// kWG / W consecutive parts, coalesced rows), in slice order; the parts are then added in
+// order and each target finishes (sg: the active list in LDS; ts: the corrector's inputs
+// of target tid, held by thread tid, or null).
 template <class V, int NEWTON>
 __device__ __forceinline__ void small_reduce_last(const ForceArgs &A, const int *sg,
                                                   const TargetState *ts = nullptr) {
   __shared__ double sums[kWG];
   const int tid = threadIdx.x;
-  const int W = 4 * A.n_act, P = kWG / W, S = A.plan.n_slices;
+  const int W = 4 * A.n_act, S = A.plan.n_slices, P = min(kWG / W, S);
   const int L = (S + P - 1) / P;
   const int p = tid / W, v = tid - p * W;
   double s = 0.0;
   if (p < P) {
     const int s1 = min(S, (p + 1) * L);
-#pragma unroll 8
-    for (int sl = p * L; sl < s1; ++sl) s += A.part[static_cast<int64_t>(sl) * W + v];
+#pragma unroll 16
+    for (int sl = p * L; sl < s1; ++sl)
+      s += load_partial(&A.part[static_cast<int64_t>(sl) * W + v]);
   }
   sums[tid] = s;
   __syncthreads();
@@ -406,7 +407,7 @@ __global__ __launch_bounds__(kWG) void k_force_small(ForceArgs A) {
   }
   __syncthreads();
   small_tile_sums<V, NEWTON>(A, si, sg, J, j, tile);
-  if (A.fuse_reduce && last_workgroup(A.done)) small_reduce_last<V, NEWTON>(A, sg);
+  if (A.fuse_reduce && last_workgroup_partials(A.done)) small_reduce_last<V, NEWTON>(A, sg);
 }
 
 // Source record of a policy built from a particle's predicted position and mass: the
@@ -503,7 +504,10 @@ __global__ __launch_bounds__(kWG) void k_force_small_pred(ForceArgs A, PredictAr
   if (blockIdx.x == 0) store_inline_idx(in, tid);
   __syncthreads();
   small_tile_sums<V, NEWTON>(A, si, sg, J, j, tile);
-  if (!A.fuse_reduce || !last_workgroup(A.done)) return;
+  // (the criterion also reads the planes the other workgroups stored)
+  if (!A.fuse_reduce ||
+      !(A.crit.on ? last_workgroup(A.done) : last_workgroup_partials(A.done)))
+    return;
   small_reduce_last<V, NEWTON>(A, sg, &ts);
   if (A.crit.on) small_criterion_last<V>(A, sg);
 }

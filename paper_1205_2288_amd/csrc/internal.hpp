@@ -135,53 +135,125 @@ __device__ __forceinline__ double ff_weight(double m) {
   return m > 0.0 ? 1.0 / cbrt(m * m) : __builtin_inf();
 }
 
+// Combination of lanes O apart (O = 32, 16, ..., 1) without LDS where the hardware has such
+// a move: the halves and the odd and even rows of 16 lanes change places between two
+// registers (v_permlane32_swap, v_permlane16_swap), lanes 8, 2 and 1 apart come as an
+// operand (DPP row rotation and quad permutation); only 4 apart is an LDS swizzle.  A
+// butterfly of ds_bpermute shuffles took 5 LDS round trips more.
+// lane_fold: every lane with bit O clear gets op over both lanes' a, the others over b.
+template <int O>
+__device__ __forceinline__ int lane_move(int x) {
+  if constexpr (O == 8) return __builtin_amdgcn_update_dpp(0, x, 0x128, 0xf, 0xf, true);
+  else if constexpr (O == 4) return __builtin_amdgcn_ds_swizzle(x, 0x101f);
+  else if constexpr (O == 2) return __builtin_amdgcn_update_dpp(0, x, 0x4e, 0xf, 0xf, true);
+  else return __builtin_amdgcn_update_dpp(0, x, 0xb1, 0xf, 0xf, true);
+}
+template <int O>
+__device__ __forceinline__ float lane_move(float x) {
+  return __builtin_bit_cast(float, lane_move<O>(__builtin_bit_cast(int, x)));
+}
+template <int O>
+__device__ __forceinline__ double lane_move(double x) {
+  int2 v = __builtin_bit_cast(int2, x);
+  v.x = lane_move<O>(v.x);
+  v.y = lane_move<O>(v.y);
+  return __builtin_bit_cast(double, v);
+}
+template <int O>
+__device__ __forceinline__ void lane_swap(unsigned &a, unsigned &b) {
+  static_assert(O == 32 || O == 16, "halves or rows");
+  // two registers whatever the compiler knows of the values: the move writes both, and
+  // equal operands were seen to be given one register
+  asm("" : "+v"(b));
+  if constexpr (O == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    a = r[0];
+    b = r[1];
+  }
+}
+template <int O>
+__device__ __forceinline__ void lane_swap(float &a, float &b) {
+  unsigned u = __float_as_uint(a), v = __float_as_uint(b);
+  lane_swap<O>(u, v);
+  a = __uint_as_float(u);
+  b = __uint_as_float(v);
+}
+template <int O>
+__device__ __forceinline__ void lane_swap(double &a, double &b) {
+  uint2 u = __builtin_bit_cast(uint2, a), v = __builtin_bit_cast(uint2, b);
+  lane_swap<O>(u.x, v.x);
+  lane_swap<O>(u.y, v.y);
+  a = __builtin_bit_cast(double, u);
+  b = __builtin_bit_cast(double, v);
+}
+template <int O, class T, class Op>
+__device__ __forceinline__ T lane_fold(T a, T b, int lane, Op op) {
+  if constexpr (O >= 16) {
+    lane_swap<O>(a, b);
+    return op(a, b);
+  } else {
+    // both read first: a select between array elements would become a select of
+    // addresses, which keeps a float64 array out of registers
+    const bool up = (lane & O) != 0;
+    const T keep = up ? b : a;
+    const T send = up ? a : b;
+    return op(keep, lane_move<O>(send));
+  }
+}
+// Every lane's x combined with that of the lane O apart.
+template <int O, class T, class Op>
+__device__ __forceinline__ T lane_pair(T x, Op op) {
+  if constexpr (O >= 16) {
+    T y = x;
+    lane_swap<O>(x, y);
+    return op(x, y);
+  } else {
+    return op(x, lane_move<O>(x));
+  }
+}
+
 // Fixed-order butterfly reductions over one wave64 (every lane receives the result).
-__device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off, 64);
+template <int O, class T, class Op>
+__device__ __forceinline__ T wave_combine(T x, Op op) {
+  x = lane_pair<O>(x, op);
+  if constexpr (O > 1) x = wave_combine<O / 2>(x, op);
   return x;
+}
+__device__ __forceinline__ double wave_sum(double x) {
+  return wave_combine<32>(x, [](double a, double b) { return a + b; });
 }
 __device__ __forceinline__ double wave_max(double x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x = fmax(x, __shfl_xor(x, off, 64));
-  return x;
+  return wave_combine<32>(x, [](double a, double b) { return fmax(a, b); });
 }
 __device__ __forceinline__ double wave_min(double x) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) x = fmin(x, __shfl_xor(x, off, 64));
-  return x;
+  return wave_combine<32>(x, [](double a, double b) { return fmin(a, b); });
 }
 
 // Reduction over one wave64 of NV values per lane (NV a power of two, at most 64) by
 // recursive halving: at each of the log2(NV) stages a lane keeps half of its values and
-// combines them with its partner's copies of the same values (one shuffle per kept value,
-// 63 shuffles for 64 values where separate butterflies take 384); the remaining stages
-// combine the one value left across lanes.  Lane l returns value l >> (6 - log2 NV),
-// combined over all 64 lanes (the same in every lane of its group); x is consumed.
+// combines them with its partner's copies of the same values (63 moves for 64 values where
+// separate butterflies take 384); the remaining stages combine the one value left across
+// lanes.  Lane l returns value l >> (6 - log2 NV), combined over all 64 lanes (the same in
+// every lane of its group); x is consumed.
+template <int O, int NV, class T, class Op>
+__device__ __forceinline__ void halve(T *x, int lane, Op op) {
+  if constexpr (NV > 1) {
+#pragma unroll
+    for (int i = 0; i < NV / 2; ++i) x[i] = lane_fold<O>(x[i], x[NV / 2 + i], lane, op);
+    if constexpr (O > 1) halve<O / 2, NV / 2>(x, lane, op);
+  } else {
+    x[0] = wave_combine<O>(x[0], op);
+  }
+}
 template <int NV, class T, class Op>
 __device__ __forceinline__ T wave_reduce_many(T (&x)[NV], int lane, Op op) {
   static_assert(NV >= 1 && NV <= 64 && (NV & (NV - 1)) == 0, "power of two up to 64");
-  constexpr int M = NV == 1 ? 0 : NV == 2 ? 1 : NV == 4 ? 2 : NV == 8 ? 3 : NV == 16 ? 4
-                  : NV == 32 ? 5 : 6;
-#pragma unroll
-  for (int s = 0; s < M; ++s) {
-    const int o = 32 >> s;
-    const int half = NV >> (s + 1);
-    const bool up = (lane & o) != 0;
-#pragma unroll
-    for (int i = 0; i < half; ++i) {
-      // both elements read first: a select between array elements would become a select
-      // of addresses, which keeps a float64 array out of registers
-      const T a = x[i], b = x[half + i];
-      const T keep = up ? b : a;
-      const T send = up ? a : b;
-      x[i] = op(keep, __shfl_xor(send, o, 64));
-    }
-  }
-  T r = x[0];
-#pragma unroll
-  for (int o = 32 >> M; o >= 1; o >>= 1) r = op(r, __shfl_xor(r, o, 64));
-  return r;
+  halve<32, NV>(x, lane, op);
+  return x[0];
 }
 
 // Whether this workgroup is the last of its launch (a one-dimensional grid) to get here,
@@ -204,6 +276,32 @@ __device__ __forceinline__ bool last_workgroup(uint32_t *done) {
   if (!last) return false;
   __threadfence();
   return true;
+}
+
+// The same where everything the last workgroup reads of the others' was written by
+// store_partial and is read by load_partial: those pass the caches that the XCDs do not
+// share (relaxed atomics of agent scope), so no cache is written back or emptied; every
+// thread waits until its stores have arrived before the workgroup is counted.  With the
+// register moves above instead of LDS shuffles, small calls on N = 4096 took (us, force /
+// criterion): 4 targets 7.0 / 8.0 -> 5.1 / 5.7, 16 targets 9.7 / 8.9 -> 7.3 / 6.9; one
+// target, whose 64 mostly empty parts are no longer added, 8.7 / 10.3 -> 4.7 / 5.3.
+__device__ __forceinline__ void store_partial(double *p, double x) {
+  __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double load_partial(const double *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool last_workgroup_partials(uint32_t *done) {
+  __shared__ uint32_t last;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t before = atomicAdd(done, 1u);
+    last = before + 1 == gridDim.x ? 1u : 0u;
+    if (last) atomicExch(done, 0u);
+  }
+  __syncthreads();
+  return last != 0;
 }
 
 // Split-j partials are combined by one thread per target when there are few slices and
@@ -229,10 +327,8 @@ __host__ __device__ inline bool use_rows_reduce(int n_slices, int64_t n_targets)
 
 // The small-set kernels' last workgroup reduces the partials (W values per slice) itself
 // when the launch has at most kFuseSlices workgroups and each of its threads then reads
-// at most kFuseLoads partials; otherwise a reduction kernel follows.  Every workgroup of a
-// fused launch pays an agent-scope fence (an L2 write-back on this multi-XCD part): at 16
-// workgroups that costs less than a second launch, at 512 (N = 131072) it costs 20 us
-// more.
+// at most kFuseLoads partials; otherwise a reduction kernel follows (512 workgroups, N =
+// 131072, would leave the last one four times the loads in flight at a time).
 constexpr int kFuseLoads = 32;
 constexpr int kFuseSlices = 64;
 __host__ __device__ inline bool fuse_small_reduce(int n_slices, int W) {

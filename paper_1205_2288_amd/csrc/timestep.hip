@@ -247,21 +247,21 @@ __global__ __launch_bounds__(kWG) void k_timestep_small(StepArgs A) {
     for (int ww = 1; ww < kWG / 64; ++ww)
       s = c == 0 ? fmax(s, static_cast<double>(red[q][c][ww]))
                  : fmin(s, static_cast<double>(red[q][c][ww]));
-    A.part[(static_cast<int64_t>(tile) * 2 + c) * A.n_act + q] = s;
+    store_partial(&A.part[(static_cast<int64_t>(tile) * 2 + c) * A.n_act + q], s);
   }
-  if (!A.fuse_reduce || !last_workgroup(A.done)) return;
+  if (!A.fuse_reduce || !last_workgroup_partials(A.done)) return;
   // the launch's last workgroup: a slice's partials form a row of W = 2 n_act values (the
   // maxima, then the minima); thread t combines value t % W over part t / W of the slices
-  const int W = 2 * A.n_act, P = kWG / W, S = A.plan.n_slices;
+  const int W = 2 * A.n_act, S = A.plan.n_slices, P = min(kWG / W, S);
   const int L = (S + P - 1) / P;
   const int p = tid / W, vv = tid - p * W;
   const bool is_max = vv < A.n_act;
   double acc = is_max ? 0.0 : __builtin_inf();
   if (p < P) {
     const int s1 = min(S, (p + 1) * L);
-#pragma unroll 8
+#pragma unroll 16
     for (int sl = p * L; sl < s1; ++sl) {
-      const double x = A.part[static_cast<int64_t>(sl) * W + vv];
+      const double x = load_partial(&A.part[static_cast<int64_t>(sl) * W + vv]);
       acc = is_max ? fmax(acc, x) : fmin(acc, x);
     }
   }
