@@ -473,9 +473,10 @@ int tsbts_force_criterion(tsbts_ctx *c, const int32_t *idx, int32_t n_act, doubl
   if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, TSBTS_EINVAL, "eta must be > 0");
   if (int s = check_pred(c, t_block)) return s;
   hipError_t e;
-  if (n_act <= kSmallAct) {
-    // small sets: the j-parallel criterion and force kernels, criterion first, on the same
-    // predicted state (same definition as the fused pass, fewer idle lanes)
+  if (n_act <= kSmallAct || share_force(c, n_act).chunk) {
+    // small sets, and sets whose targets the waves share: the criterion and force kernels,
+    // criterion first, on the same predicted state (same definition as the fused pass,
+    // fewer idle lanes)
     if (int s = ensure_part(c, partial_elems_needed(c, n_act))) return s;
     e = launch_timestep(c, idx, n_act, eta, dtc, stream);
     if (e == hipSuccess) e = launch_force(c, idx, n_act, acc, pot, stream);
@@ -828,7 +829,7 @@ int force_criterion_correct(tsbts_ctx *c, const int32_t *idx, int32_t n_act, dou
     corr.step = tags->step;
   }
   hipError_t e;
-  if (n_act <= kSmallAct) {
+  if (n_act <= kSmallAct || share_force(c, n_act).chunk) {
     // small sets: the criterion on the predicted state first, then the force with the
     // corrector (the corrector rewrites the velocities the criterion reads)
     e = launch_timestep(c, idx, n_act, eta, dtc, stream);

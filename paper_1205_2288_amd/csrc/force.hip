@@ -60,6 +60,7 @@ struct ForceArgs {
   int ipl;       // targets per lane
   int scalar_j;  // j-particles through scalar loads (k_force_scalar)
   int chunk;     // j-particles per split unit of k_force_scalar
+  ShareShape share;  // the split when its waves share the targets
   int correct;   // apply the corrector to each target as its force is finished
   CorrectArgs corr;
   uint32_t *done;   // finished-workgroup count of the small-set kernels
@@ -195,8 +196,10 @@ __device__ __forceinline__ void scalar_tile(const ForceArgs &A, const typename V
   }
 }
 
-// Split units of CH j-particles (A.n_jtiles counts them here).
-template <class V, int NEWTON, int POT, int CH>
+// Split units of SH * CH j-particles (A.n_jtiles counts them here): with SH = 1 a target
+// per lane of the workgroup, with SH = kShare a target per lane of every wave, wave w
+// taking part w of each unit; the waves' float64 sums are then added in wave order.
+template <class V, int NEWTON, int POT, int CH, int SH>
 __global__ __launch_bounds__(kWG) void k_force_scalar(ForceArgs A) {
   using F = typename V::F;
   int itile, slice;
@@ -205,13 +208,16 @@ __global__ __launch_bounds__(kWG) void k_force_scalar(ForceArgs A) {
   const int jt0 = slice * A.plan.tiles_per_slice;
   const int jt1 = min(jt0 + A.plan.tiles_per_slice, A.n_jtiles);
   const F eps2 = sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2);
-  const int q = itile * kWG + static_cast<int>(threadIdx.x);
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  const int w = SH == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q = SH == 1 ? itile * kWG + static_cast<int>(threadIdx.x) : itile * 64 + lane;
   const int g = A.idx[min(q, A.n_act - 1)];
   const typename V::I I = V::load_i(A.p32, A.p64, A.npad, g);
   const int gs = A.self ? g : -1;  // the target's index among the sources
   double sx = 0.0, sy = 0.0, sz = 0.0, sp = 0.0;
   for (int jt = jt0; jt < jt1; ++jt) {
-    const int64_t jbase = static_cast<int64_t>(jt) * CH;
+    const int64_t jbase = (static_cast<int64_t>(jt) * SH + w) * CH;
+    if (SH > 1 && jbase >= A.snpad) break;
     F fx = F(0), fy = F(0), fz = F(0), fp = F(0);
     if (__ballot(gs >= jbase && gs < jbase + CH) != 0)
       scalar_tile<V, NEWTON, 1, POT, CH>(A, I, gs, jbase, eps2, fx, fy, fz, fp);
@@ -221,6 +227,22 @@ __global__ __launch_bounds__(kWG) void k_force_scalar(ForceArgs A) {
     sy += static_cast<double>(fy);
     sz += static_cast<double>(fz);
     sp += static_cast<double>(fp);
+  }
+  if constexpr (SH > 1) {
+    __shared__ double red[SH][4][64];
+    red[w][0][lane] = sx;
+    red[w][1][lane] = sy;
+    red[w][2][lane] = sz;
+    red[w][3][lane] = sp;
+    __syncthreads();
+    if (w > 0) return;
+#pragma unroll
+    for (int u = 1; u < SH; ++u) {
+      sx += red[u][0][lane];
+      sy += red[u][1][lane];
+      sz += red[u][2][lane];
+      sp += red[u][3][lane];
+    }
   }
   if (q >= A.n_act) return;
   if (A.plan.n_slices == 1) {
@@ -609,20 +631,32 @@ hipError_t run_scalar(ForceArgs &A, hipStream_t st) {
     A.snpad = A.npad;
     A.self = 1;
   }
-  A.n_jtiles = static_cast<int>(A.snpad / A.chunk);
-  A.plan = plan_split(A.n_act, 1, A.n_jtiles, A.blocks);
-  const dim3 grid(A.plan.nblk), block(kWG);
-  if (A.chunk == kChunkSmall) {
-    if (A.pot)
-      hipLaunchKernelGGL((k_force_scalar<V, NEWTON, 1, kChunkSmall>), grid, block, 0, st, A);
-    else
-      hipLaunchKernelGGL((k_force_scalar<V, NEWTON, 0, kChunkSmall>), grid, block, 0, st, A);
+  int chunk = A.chunk;
+  if (A.share.chunk) {
+    chunk = A.share.chunk;
+    A.n_jtiles = A.share.n_units;
+    A.plan = A.share.plan;
   } else {
-    if (A.pot)
-      hipLaunchKernelGGL((k_force_scalar<V, NEWTON, 1, kTJ>), grid, block, 0, st, A);
-    else
-      hipLaunchKernelGGL((k_force_scalar<V, NEWTON, 0, kTJ>), grid, block, 0, st, A);
+    A.n_jtiles = static_cast<int>(A.snpad / chunk);
+    A.plan = plan_split(A.n_act, 1, A.n_jtiles, A.blocks);
   }
+  const dim3 grid(A.plan.nblk), block(kWG);
+  auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, A); };
+  const bool pot = A.pot != nullptr;
+  if (A.share.chunk == kChunkTiny)
+    launch(pot ? k_force_scalar<V, NEWTON, 1, kChunkTiny, kShare>
+               : k_force_scalar<V, NEWTON, 0, kChunkTiny, kShare>);
+  else if (A.share.chunk == kChunkSmall)
+    launch(pot ? k_force_scalar<V, NEWTON, 1, kChunkSmall, kShare>
+               : k_force_scalar<V, NEWTON, 0, kChunkSmall, kShare>);
+  else if (A.share.chunk)
+    launch(pot ? k_force_scalar<V, NEWTON, 1, kTJ, kShare>
+               : k_force_scalar<V, NEWTON, 0, kTJ, kShare>);
+  else if (chunk == kChunkSmall)
+    launch(pot ? k_force_scalar<V, NEWTON, 1, kChunkSmall, 1>
+               : k_force_scalar<V, NEWTON, 0, kChunkSmall, 1>);
+  else
+    launch(pot ? k_force_scalar<V, NEWTON, 1, kTJ, 1> : k_force_scalar<V, NEWTON, 0, kTJ, 1>);
   return launch_reduce<V, NEWTON>(A, st);
 }
 
@@ -683,9 +717,51 @@ SplitPlan plan_split(int64_t n_targets, int ipl, int64_t n_jtiles, int target_bl
   return p;
 }
 
+namespace {
+
+ShareShape share_shape(const tsbts_ctx *c, int n_act, int chunk) {
+  ShareShape s;
+  const int64_t itiles = (n_act + 63) / 64;
+  if (!chunk)
+    chunk = itiles * (c->npad / (kShare * kChunkSmall)) < 512 ? kChunkTiny : kChunkSmall;
+  s.chunk = chunk;
+  s.n_units = static_cast<int>((c->npad + kShare * chunk - 1) / (kShare * chunk));
+  // about 2048 workgroups, and few slices for the rows reduction: at most half of what it
+  // takes unless each would hold several units
+  const int64_t cap = s.n_units >= 2 * kRowsFewSlices ? kRowsFewSlices : kRowsFewSlices / 2;
+  const int64_t want = std::min<int64_t>((2048 + itiles - 1) / itiles, cap);
+  const int64_t slices = std::max<int64_t>(1, std::min<int64_t>(want, s.n_units));
+  s.plan.n_itiles = static_cast<int>(itiles);
+  s.plan.tiles_per_slice = static_cast<int>((s.n_units + slices - 1) / slices);
+  s.plan.n_slices = (s.n_units + s.plan.tiles_per_slice - 1) / s.plan.tiles_per_slice;
+  s.plan.nblk = static_cast<int>(round_up(itiles * s.plan.n_slices, 8));
+  return s;
+}
+
+bool share_applies(const tsbts_ctx *c, int n_act) {
+  return force_scalar_j(c) && c->tune_chunk == 0 && n_act < kShareMaxAct;
+}
+
+}  // namespace
+
+ShareShape share_force(const tsbts_ctx *c, int n_act) {
+  if (!share_applies(c, n_act)) return ShareShape{};
+  return share_shape(c, n_act, c->precision == TSBTS_FP64 ? 0 : scalar_chunk(c, n_act, 1));
+}
+
+ShareShape share_step(const tsbts_ctx *c, int n_act) {
+  // mixed, many particles: above 256 targets the LDS-staged kernel, whose vector operands
+  // issue faster than scalar ones (512 targets at N = 131072 54 against 62 us)
+  const bool staged = c->precision == TSBTS_MIXED && c->npad >= 65536 && n_act > 256;
+  if (!share_applies(c, n_act) || staged) return ShareShape{};
+  return share_shape(c, n_act, 0);
+}
+
 int64_t force_partial_elems(const tsbts_ctx *c, int n_act, int blocks) {
   // small sets: one partial per j-tile and target
   if (n_act <= small_act_limit(c)) return c->npad / kTJ * 4 * n_act;
+  const ShareShape sh = share_force(c, n_act);
+  if (sh.chunk) return static_cast<int64_t>(sh.plan.n_slices) * 4 * n_act;
   const SplitPlan pf =
       force_scalar_j(c)
           ? plan_split(n_act, 1, c->npad / scalar_chunk(c, n_act, 1), blocks)
@@ -698,6 +774,9 @@ int64_t partial_elems_needed(const tsbts_ctx *c, int n_act) {
   const int64_t need_f = force_partial_elems(c, n_act, c->tune_blocks);
   // the criterion: small sets one partial per j-tile with 2 values per target
   if (n_act <= kSmallAct) return std::max(need_f, n_jtiles * 2 * n_act);
+  const ShareShape sh = share_step(c, n_act);
+  if (sh.chunk)
+    return std::max(need_f, static_cast<int64_t>(sh.plan.n_slices) * 2 * n_act);
   const int ipl_c = criterion_targets_per_lane(c, n_act);
   const int64_t units_c =
       criterion_scalar_j(c, n_act) ? c->npad / scalar_chunk(c, n_act, ipl_c) : n_jtiles;
@@ -728,12 +807,13 @@ hipError_t launch_force_gather(tsbts_ctx *c, const int32_t *idx, int n_act, doub
   A.ipl = force_targets_per_lane(c, n_act);
   A.scalar_j = force_scalar_j(c) ? 1 : 0;
   A.chunk = scalar_chunk(c, n_act, 1);
+  A.share = share_force(c, n_act);
   A.done = c->done;
   A.fuse_reduce = 0;
   if (src) {
-    // the scalar-load kernel over the given sources (more targets than the small-set
-    // kernels take: split calls only)
-    if (n_act <= small_act_limit(c)) return hipErrorInvalidValue;
+    // the scalar-load kernel over the given sources with a target per lane of the
+    // workgroup (split calls only)
+    if (n_act < kShareMaxAct) return hipErrorInvalidValue;
     A.s32 = src->p32;
     A.s64 = src->p64;
     A.snpad = src->npad;

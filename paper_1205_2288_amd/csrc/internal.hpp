@@ -319,10 +319,13 @@ __host__ __device__ inline bool use_wave_reduce(int n_slices, int64_t n_targets)
 // wave-per-target form touches a cache line per 8-byte partial).  Below that there are
 // too few such workgroups (at 256 targets 4, each wave walking 128 slices: 43 against
 // 34 us per call at N = 131072).
+// With at most kRowsFewSlices slices a wave walks few of them whatever the target count.
 constexpr int64_t kRowsReduceMinTargets = 2048;
 constexpr int kRowsWaves = 16;
+constexpr int kRowsFewSlices = 256;
 __host__ __device__ inline bool use_rows_reduce(int n_slices, int64_t n_targets) {
-  return n_slices >= kWaveReduceSlices && n_targets >= kRowsReduceMinTargets;
+  return n_slices >= kWaveReduceSlices &&
+         (n_targets >= kRowsReduceMinTargets || n_slices <= kRowsFewSlices);
 }
 
 // The small-set kernels' last workgroup reduces the partials (W values per slice) itself
@@ -385,18 +388,39 @@ inline bool force_scalar_j(const tsbts_ctx *c) { return c->tune_ipl == 0; }
 inline int force_targets_per_lane(const tsbts_ctx *c, int n_act) {
   return force_scalar_j(c) ? 1 : targets_per_lane(c, n_act);
 }
-// j-particles per split unit of the scalar-load kernels: whole tiles of kTJ, or quarter
-// tiles when whole tiles would give too few workgroups to fill the chip (small N or small
-// active sets), so that the j-range splits over 4x more workgroups.
+// j-particles per split unit of the scalar-load kernels with a target per lane of the
+// workgroup: whole tiles of kTJ, or quarter tiles when whole tiles would give too few
+// workgroups to fill the chip, so that the j-range splits over 4x more workgroups.
 constexpr int kChunkSmall = 64;
 inline int scalar_chunk(const tsbts_ctx *c, int n_act, int ipl) {
   if (c->tune_chunk) return c->tune_chunk;
   const int64_t itiles = (n_act + ipl * kWG - 1) / (ipl * kWG);
   return itiles * (c->npad / kTJ) < 512 ? kChunkSmall : kTJ;
 }
+// Scalar-load kernels whose workgroup holds 64 targets, one per lane, and whose waves
+// share the j-particles of a unit (kShare parts of `chunk`): for active sets below
+// kShareMaxAct, where a target per lane of the workgroup leaves lanes without a target
+// (33 targets in 256 lanes) and many slices for the reduction to read (472 of 64
+// j-particles for 777 targets at N = 30011).  Measured (us, force / criterion, the other
+// form first): mixed 64 targets N = 256 8.7 / 11.7 and 7.1 / 7.1, 1500 targets N = 4096
+// 13.4 / 14.4 and 9.8 / 10.9, 777 targets N = 30011 36 / 33 and 21 / 24; float64 64
+// targets N = 131072 39 / 45 and 23 / 24, 3000 targets N = 16384 45 / 54 and 41 / 46; from
+// 4096 targets the other form is as fast or faster.  A tuned shape keeps the other form.
+//   The j-particles per wave are the other form's chunk in the mixed force (its float32
+// sums stay the same numbers; only float64 sums are regrouped), else 64, or 16 where
+// units of 4 x 64 would be fewer than 512 workgroups.
+constexpr int kShare = kWG / 64;
+constexpr int kShareMaxAct = 4096;
+constexpr int kChunkTiny = 16;
+struct ShareShape {
+  int chunk;       // j-particles per wave and unit; 0: not this form
+  int n_units;     // units of kShare * chunk (the last one may pass the padding)
+  SplitPlan plan;  // n_itiles counts 64 targets
+};
+ShareShape share_force(const tsbts_ctx *c, int n_act);
+ShareShape share_step(const tsbts_ctx *c, int n_act);
 // The criterion kernel likewise for large active sets (from 8192 targets, two targets per
-// lane, twice the workgroups) and for small launches (one target per lane, quarter-tile
-// units); in between the LDS-staged kernel with one target per lane measured faster.
+// lane, twice the workgroups).
 inline bool criterion_scalar_j(const tsbts_ctx *c, int n_act) {
   return force_scalar_j(c) && (n_act >= 8192 || scalar_chunk(c, n_act, 1) == kChunkSmall);
 }

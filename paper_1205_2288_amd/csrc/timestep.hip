@@ -34,6 +34,7 @@ struct StepArgs {
   int ipl;
   int scalar_j;  // j-particles through scalar loads (k_timestep_scalar)
   int chunk;     // j-particles per split unit of k_timestep_scalar
+  ShareShape share;  // the split when its waves share the targets
   uint32_t *done;   // finished-workgroup count of k_timestep_small
   int fuse_reduce;  // its last workgroup reduces the partials
   // Sources of k_timestep_scalar (null s64: the predicted arrays above): sn particles,
@@ -144,11 +145,14 @@ __device__ __forceinline__ void scalar_step_tile(const SrcPlanes &S, int64_t sn,
   }
 }
 
-// Split units of CH j-particles (A.n_jtiles counts them here).
-template <class V, int IPL, int CH>
+// Split units of SH * CH j-particles (A.n_jtiles counts them here), the targets per lane
+// of the workgroup (SH = 1) or of every wave (SH = kShare), as in k_force_scalar.
+template <class V, int IPL, int CH, int SH>
 __global__ __launch_bounds__(kWG) void k_timestep_scalar(StepArgs A) {
+  static_assert(SH == 1 || IPL == 1, "one shared target per lane");
   using F = typename V::F;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = SH == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int itile, slice;
   split_tile(blockIdx.x, A.plan, itile, slice);
   if (slice >= A.plan.n_slices) return;
@@ -160,7 +164,7 @@ __global__ __launch_bounds__(kWG) void k_timestep_scalar(StepArgs A) {
   F qmax[IPL], swmin[IPL];
 #pragma unroll
   for (int k = 0; k < IPL; ++k) {
-    q[k] = (itile * IPL + k) * kWG + tid;
+    q[k] = SH == 1 ? (itile * IPL + k) * kWG + tid : itile * 64 + lane;
     const int t = A.idx[min(q[k], A.n_act - 1)];
     I[k] = load_iv<V>(A, t);
     g[k] = A.self ? t : -1;  // the target's index among the sources
@@ -169,7 +173,7 @@ __global__ __launch_bounds__(kWG) void k_timestep_scalar(StepArgs A) {
   }
   const SrcPlanes S{A.s32, A.s64, A.sv64, A.snpad};
   for (int jt = jt0; jt < jt1; ++jt) {
-    const int64_t jbase = static_cast<int64_t>(jt) * CH;
+    const int64_t jbase = (static_cast<int64_t>(jt) * SH + w) * CH;
     bool mine = false;
 #pragma unroll
     for (int k = 0; k < IPL; ++k) mine |= (g[k] >= jbase && g[k] < jbase + CH);
@@ -177,6 +181,18 @@ __global__ __launch_bounds__(kWG) void k_timestep_scalar(StepArgs A) {
       scalar_step_tile<V, 1, IPL, CH>(S, A.sn, I, g, jbase, eps2, qmax, swmin);
     else
       scalar_step_tile<V, 0, IPL, CH>(S, A.sn, I, g, jbase, eps2, qmax, swmin);
+  }
+  if constexpr (SH > 1) {
+    __shared__ F red[SH][2][64];
+    red[w][0][lane] = qmax[0];
+    red[w][1][lane] = swmin[0];
+    __syncthreads();
+    if (w > 0) return;
+#pragma unroll
+    for (int u = 1; u < SH; ++u) {
+      qmax[0] = fmax(qmax[0], red[u][0][lane]);
+      swmin[0] = fmin(swmin[0], red[u][1][lane]);
+    }
   }
 #pragma unroll
   for (int k = 0; k < IPL; ++k) {
@@ -353,17 +369,25 @@ hipError_t run(StepArgs &A, hipStream_t st) {
       A.sn = A.n;
       A.self = 1;
     }
-    A.n_jtiles = static_cast<int>(A.snpad / A.chunk);
-    A.plan = plan_split(A.n_act, A.ipl, A.n_jtiles, A.blocks);
+    if (A.share.chunk) {
+      A.n_jtiles = A.share.n_units;
+      A.plan = A.share.plan;
+    } else {
+      A.n_jtiles = static_cast<int>(A.snpad / A.chunk);
+      A.plan = plan_split(A.n_act, A.ipl, A.n_jtiles, A.blocks);
+    }
     const dim3 grid(A.plan.nblk), block(kWG);
-    if (A.ipl == 2 && A.chunk == kTJ)
-      hipLaunchKernelGGL((k_timestep_scalar<V, 2, kTJ>), grid, block, 0, st, A);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, block, 0, st, A); };
+    if (A.share.chunk == kChunkTiny)
+      launch(k_timestep_scalar<V, 1, kChunkTiny, kShare>);
+    else if (A.share.chunk)
+      launch(k_timestep_scalar<V, 1, kChunkSmall, kShare>);
     else if (A.ipl == 2)
-      hipLaunchKernelGGL((k_timestep_scalar<V, 2, kChunkSmall>), grid, block, 0, st, A);
-    else if (A.chunk == kTJ)
-      hipLaunchKernelGGL((k_timestep_scalar<V, 1, kTJ>), grid, block, 0, st, A);
+      launch(A.chunk == kTJ ? k_timestep_scalar<V, 2, kTJ, 1>
+                            : k_timestep_scalar<V, 2, kChunkSmall, 1>);
     else
-      hipLaunchKernelGGL((k_timestep_scalar<V, 1, kChunkSmall>), grid, block, 0, st, A);
+      launch(A.chunk == kTJ ? k_timestep_scalar<V, 1, kTJ, 1>
+                            : k_timestep_scalar<V, 1, kChunkSmall, 1>);
   } else {
     A.plan = plan_split(A.n_act, A.ipl, A.n_jtiles, A.blocks);
     if (A.ipl == 4)
@@ -407,7 +431,8 @@ StepArgs gather_args(tsbts_ctx *c, const int32_t *idx, int n_act, double eta, do
   A.dtc = dtc;
   A.blocks = criterion_blocks(c, n_act);
   A.ipl = criterion_targets_per_lane(c, n_act);
-  A.scalar_j = criterion_scalar_j(c, n_act) ? 1 : 0;
+  A.share = share_step(c, n_act);
+  A.scalar_j = A.share.chunk || criterion_scalar_j(c, n_act) ? 1 : 0;
   A.chunk = scalar_chunk(c, n_act, A.ipl);
   A.done = c->done + 1;
   A.fuse_reduce = 0;
