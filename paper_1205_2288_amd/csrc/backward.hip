@@ -62,7 +62,7 @@ __device__ __forceinline__ typename V::F inv_r(typename V::F s) {
   if constexpr (sizeof(typename V::F) == 4) {
     return NEWTON ? 0.5f * rsq_refined<1>(s) : rsq_refined<0>(s);
   } else {
-    return rsqrt_f64<2>(s);
+    return rsqrt_f64(s);
   }
 }
 

@@ -50,7 +50,7 @@ __device__ __forceinline__ void pair_bwd_sym(const typename V::I &i, typename V:
   if constexpr (sizeof(F) == 4)
     y = rsq_f32(s);
   else
-    y = rsqrt_f64<2>(s);
+    y = rsqrt_f64(s);
   if (skip) y = F(0);
   const F y2 = y * y;
   const F y3 = y2 * y;

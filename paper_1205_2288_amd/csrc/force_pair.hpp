@@ -42,13 +42,10 @@ __device__ __forceinline__ void pair_acc(const typename V::I &i, const typename 
     s = 1.0;
     m = 0.0;
   }
-  const double y = rsqrt_f64<2>(s);
-  const double mr1 = m * y;
-  const double mr3 = mr1 * (y * y);
+  const double mr3 = scaled_inv_cube_f64<POT>(s, m, pp);
   ax = fma(mr3, dx, ax);
   ay = fma(mr3, dy, ay);
   az = fma(mr3, dz, az);
-  if (POT) pp += mr1;
 }
 
 // Mass scale held in LDS and the final acceleration scale (see rsq_refined).

@@ -72,9 +72,9 @@ __device__ __forceinline__ void pair_acc_sym(const typename V::I &i, double mi,
   double dx, dy, dz;
   V::sep(i, j, dx, dy, dz);
   const double s = fma(dx, dx, fma(dy, dy, fma(dz, dz, eps2)));
-  double y = rsqrt_f64<2>(s);
-  if (skip) y = 0.0;
-  const double y3 = y * (y * y);
+  double y = 0.0;
+  double y3 = scaled_inv_cube_f64<POT>(s, 1.0, y);
+  if (skip) y = y3 = 0.0;
   const double mj = V::mass(j);
   const double mj3 = mj * y3;
   const double mi3 = mi * y3;
