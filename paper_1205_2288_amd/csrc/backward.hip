@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_src(BwdArgs A) {
   const int64_t P = A.npad;
   const int64_t k = static_cast<int64_t>(rtile) * kWG + tid;  // row particle (< npad)
   const typename V::I row = V::load_i(A.p32, A.p64, P, k);
-  const F eps2 = static_cast<F>(A.eps2);
+  const F eps2 = in_vector(static_cast<F>(A.eps2));
   double tot[4] = {0.0, 0.0, 0.0, 0.0};
   for (int ct = ct0; ct < ct1; ++ct) {
     const int q = ct * kTJ + tid;
@@ -302,7 +302,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_tgt(BwdArgs A) {
   const F gk[4] = {static_cast<F>(A.ga[qq]), static_cast<F>(A.ga[A.n_act + qq]),
                    static_cast<F>(A.ga[2 * A.n_act + qq]),
                    static_cast<F>(A.gp ? A.gp[qq] : 0.0)};
-  const F eps2 = static_cast<F>(A.eps2);
+  const F eps2 = in_vector(static_cast<F>(A.eps2));
   double tot[3] = {0.0, 0.0, 0.0};
   for (int jt = jt0; jt < jt1; ++jt) {
     const int64_t jbase = static_cast<int64_t>(jt) * kTJ;
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_all(BwdArgs A) {
   const typename V::I row = V::load_i(A.p32, A.p64, P, k);
   const F gk[4] = {static_cast<F>(A.gord[k]), static_cast<F>(A.gord[P + k]),
                    static_cast<F>(A.gord[2 * P + k]), static_cast<F>(A.gord[3 * P + k])};
-  const F eps2 = static_cast<F>(A.eps2);
+  const F eps2 = in_vector(static_cast<F>(A.eps2));
   double tot[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   for (int jt = jt0; jt < jt1; ++jt) {
     const int64_t jbase = static_cast<int64_t>(jt) * kTJ;
@@ -483,7 +483,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_all_scalar(BwdArgs A) {
   const typename V::I row = V::load_i(A.p32, A.p64, P, k);
   const F gk[4] = {static_cast<F>(A.gord[k]), static_cast<F>(A.gord[P + k]),
                    static_cast<F>(A.gord[2 * P + k]), static_cast<F>(A.gord[3 * P + k])};
-  const F eps2 = static_cast<F>(A.eps2);
+  const F eps2 = in_vector(static_cast<F>(A.eps2));
   double tot[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   for (int jt = jt0; jt < jt1; ++jt) {
     const int64_t jbase = static_cast<int64_t>(jt) * kTJ;
@@ -538,7 +538,7 @@ hipError_t run(BwdArgs &A, hipStream_t st, tsbts_ctx *c) {
     if (bwd_sym_applies(c, A.n_act)) {
       SymPlan plan;
       if (sym_plan(c, 4, 8, c->precision == TSBTS_FP64 ? 8 : 4, &plan))
-        return launch_bwd_sym(c, plan, A.gr, A.gm, st);
+        return launch_bwd_sym(c, plan, A.gp != nullptr, A.gr, A.gm, st);
     }
     A.plan = plan_all(A);
     A.n_ctiles = static_cast<int>(A.npad / kTJ);

@@ -34,7 +34,11 @@ __global__ __launch_bounds__(kWG) void k_bwd_seeds32(int64_t len, const double *
   if (e < len) g32[e] = static_cast<float>(gord[e]);
 }
 
-template <class V>
+// GP: with the potential's seeds gi[3], gj[3].  Without, they are zero and not read, and the
+// terms of zeros are left out (the sums round the same): all of N = 131072 8.50 -> 8.15 ms
+// (float64, N = 65536: 4.50 -> 4.02; with the seeds 4.51 -> 4.35, from one barrier per 64
+// columns and a vector softening).
+template <class V, int GP>
 __device__ __forceinline__ void pair_bwd_sym(const typename V::I &i, typename V::F mi,
                                              const typename V::F (&gi)[4],
                                              const typename V::J &j,
@@ -60,8 +64,8 @@ __device__ __forceinline__ void pair_bwd_sym(const typename V::I &i, typename V:
   const F uj = fma(ex, gj[0], fma(ey, gj[1], ez * gj[2]));
   const F ui = fma(ex, gi[0], fma(ey, gi[1], ez * gi[2]));
   const F a3 = fma(P, uj, -(Q * ui));        // y^3 (m_k u_j - m_j u_k)
-  const F gs3 = fma(P, gj[3], Q * gi[3]);    // y^3 (m_k gp_j + m_j gp_k)
-  const F c = fma(F(-3) * y2, a3, -gs3);
+  F c = F(-3) * y2 * a3;
+  if (GP) c = fma(F(-3) * y2, a3, -fma(P, gj[3], Q * gi[3]));  // y^3 (m_k gp_j + m_j gp_k)
   const F tx = fma(P, gj[0], fma(-Q, gi[0], c * ex));
   const F ty = fma(P, gj[1], fma(-Q, gi[1], c * ey));
   const F tz = fma(P, gj[2], fma(-Q, gi[2], c * ez));
@@ -71,14 +75,19 @@ __device__ __forceinline__ void pair_bwd_sym(const typename V::I &i, typename V:
   cacc[0] -= tx;
   cacc[1] -= ty;
   cacc[2] -= tz;
-  acc[3] = fma(-y, fma(y2, uj, gj[3]), acc[3]);
-  cacc[3] = fma(y, fma(y2, ui, -gi[3]), cacc[3]);
+  if (GP) {
+    acc[3] = fma(-y, fma(y2, uj, gj[3]), acc[3]);
+    cacc[3] = fma(y, fma(y2, ui, -gi[3]), cacc[3]);
+  } else {
+    acc[3] = fma(-y, y2 * uj, acc[3]);
+    cacc[3] = fma(y, y2 * ui, cacc[3]);
+  }
 }
 
 // columns per LDS transposition: 8 of float32, 4 of float64 (same LDS bytes)
 template <class F> struct BCols { static constexpr int kBlock = sizeof(F) == 4 ? 8 : 4; };
 
-template <class V, int MASK>
+template <class V, int GP, int MASK>
 __device__ __forceinline__ void bwd_block(const BwdSymArgs &A, const typename V::F *g,
                                           const typename V::I (&rows)[kSymRows],
                                           const typename V::F (&mr)[kSymRows],
@@ -87,17 +96,19 @@ __device__ __forceinline__ void bwd_block(const BwdSymArgs &A, const typename V:
                                           typename V::F (&a)[kSymRows][4], typename V::F *L,
                                           int lane) {
   using F = typename V::F;
-  const F eps2 = sizeof(F) == 4 ? static_cast<F>(A.eps2) : static_cast<F>(A.eps2_64);
+  const F eps2 =
+      in_vector(sizeof(F) == 4 ? static_cast<F>(A.eps2) : static_cast<F>(A.eps2_64));
 #pragma unroll 2
   for (int c = 0; c < BCols<F>::kBlock; ++c) {
     const int64_t j = jb + c;
     const typename V::J Jr = V::load_j(A.p32, A.p64, A.npad, j, 1.0f);
-    const F gj[4] = {g[j], g[A.npad + j], g[2 * A.npad + j], g[3 * A.npad + j]};
+    const F gj[4] = {g[j], g[A.npad + j], g[2 * A.npad + j],
+                     GP ? g[3 * A.npad + j] : F(0)};
     F ca[4] = {F(0), F(0), F(0), F(0)};
 #pragma unroll
     for (int r = 0; r < kSymRows; ++r) {
       const bool skip = MASK && (j <= k[r] || j >= A.n || k[r] >= A.n);
-      pair_bwd_sym<V>(rows[r], mr[r], gr[r], Jr, gj, eps2, skip, a[r], ca);
+      pair_bwd_sym<V, GP>(rows[r], mr[r], gr[r], Jr, gj, eps2, skip, a[r], ca);
     }
     F *e = L + (c * kSymLdsStride + lane) * 4;
     e[0] = ca[0];
@@ -107,7 +118,7 @@ __device__ __forceinline__ void bwd_block(const BwdSymArgs &A, const typename V:
   }
 }
 
-template <class V>
+template <class V, int GP>
 __global__ __launch_bounds__(kWG) void k_bwd_sym(BwdSymArgs A0, const float *__restrict__ p32,
                                                  const double *__restrict__ p64,
                                                  const typename V::F *__restrict__ g32,
@@ -119,7 +130,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_sym(BwdSymArgs A0, const float *__r
   BwdSymArgs A = A0;
   A.p32 = p32;
   A.p64 = p64;
-  __shared__ F xs[2][kSymWaves][4][BLK];
+  __shared__ F xs[2][kSymWaves][4][64];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int4 it = A.plan.items[blockIdx.x];  // one work item per workgroup
@@ -145,7 +156,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_sym(BwdSymArgs A0, const float *__r
         mr[r] = A.p64[P64_M * A.npad + kk];
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        gr[r][v] = g32[v * A.npad + kk];
+        gr[r][v] = GP || v < 3 ? g32[v * A.npad + kk] : F(0);
         tot[r][v] = 0.0;
       }
     }
@@ -156,22 +167,25 @@ __global__ __launch_bounds__(kWG) void k_bwd_sym(BwdSymArgs A0, const float *__r
       for (int r = 0; r < kSymRows; ++r)
 #pragma unroll
         for (int v = 0; v < 4; ++v) a[r][v] = F(0);
+#pragma unroll 1
       for (int64_t jb = jt; jb < jt + 64; jb += BLK) {
         if (rows_pad || jb < row0 + kSymWaveRows || jb + BLK > A.n)
-          bwd_block<V, 1>(A, g32, rows, mr, gr, k, jb, a, L, lane);
+          bwd_block<V, GP, 1>(A, g32, rows, mr, gr, k, jb, a, L, lane);
         else
-          bwd_block<V, 0>(A, g32, rows, mr, gr, k, jb, a, L, lane);
+          bwd_block<V, GP, 0>(A, g32, rows, mr, gr, k, jb, a, L, lane);
         wave_lds_sync();
         F cs[4];
         sym_col_sums<BLK, 4>(L, lane, cs);
-        sym_group_store<BLK, 4>(xs, buf, wv, lane, cs, cpart + jb, A.npad,
-                                [](F x, F y) { return x + y; }, sub > 0);
+        sym_keep<BLK, 4>(xs[buf], wv, lane, static_cast<int>(jb - jt), cs);
         wave_lds_sync();
       }
 #pragma unroll
       for (int r = 0; r < kSymRows; ++r)
 #pragma unroll
         for (int v = 0; v < 4; ++v) tot[r][v] += static_cast<double>(a[r][v]);
+      sym_group_store<4>(xs[buf], wv, lane, cpart + jt, A.npad, [](F x, F y) { return x + y; },
+                         sub > 0);
+      buf ^= 1;
     }
 #pragma unroll
     for (int r = 0; r < kSymRows; ++r)
@@ -199,7 +213,7 @@ __global__ __launch_bounds__(kWG) void k_bwd_sym_reduce(BwdSymArgs A) {
 }
 
 template <class V>
-hipError_t run(BwdSymArgs &A, hipStream_t st) {
+hipError_t run(BwdSymArgs &A, bool gp, hipStream_t st) {
   using F = typename V::F;
   const F *g;
   if constexpr (sizeof(F) == 4) {
@@ -212,9 +226,14 @@ hipError_t run(BwdSymArgs &A, hipStream_t st) {
     g = A.gord;
   }
   const int nb = A.plan.n_items;  // one work item per workgroup
-  hipLaunchKernelGGL((k_bwd_sym<V>), dim3(nb), dim3(kWG), 0, st, A, A.p32, A.p64, g,
-                     static_cast<F *>(A.plan.col_part),
-                     static_cast<double *>(A.plan.row_part));
+  F *cp = static_cast<F *>(A.plan.col_part);
+  double *rp = static_cast<double *>(A.plan.row_part);
+  if (gp)
+    hipLaunchKernelGGL((k_bwd_sym<V, 1>), dim3(nb), dim3(kWG), 0, st, A, A.p32, A.p64, g, cp,
+                       rp);
+  else
+    hipLaunchKernelGGL((k_bwd_sym<V, 0>), dim3(nb), dim3(kWG), 0, st, A, A.p32, A.p64, g, cp,
+                       rp);
   hipLaunchKernelGGL(k_bwd_sym_reduce<F>, dim3(static_cast<unsigned>((A.n + kWG - 1) / kWG)),
                      dim3(kWG), 0, st, A);
   return hipGetLastError();
@@ -227,7 +246,7 @@ bool bwd_sym_applies(const tsbts_ctx *c, int64_t n_act) {
 }
 
 // After k_bwd_order has put the seeds in particle order (gord).
-hipError_t launch_bwd_sym(tsbts_ctx *c, const SymPlan &plan, double *gr, double *gm,
+hipError_t launch_bwd_sym(tsbts_ctx *c, const SymPlan &plan, bool gp, double *gr, double *gm,
                           hipStream_t st) {
   BwdSymArgs A;
   A.n = c->n;
@@ -240,9 +259,9 @@ hipError_t launch_bwd_sym(tsbts_ctx *c, const SymPlan &plan, double *gr, double 
   A.plan = plan;
   A.gr = gr;
   A.gm = gm;
-  if (c->precision == TSBTS_FP64) return run<Fp64>(A, st);
-  if (c->flags & TSBTS_FLAG_HILO_SEPARATION) return run<MixHiLo>(A, st);
-  return run<MixSep64>(A, st);
+  if (c->precision == TSBTS_FP64) return run<Fp64>(A, gp, st);
+  if (c->flags & TSBTS_FLAG_HILO_SEPARATION) return run<MixHiLo>(A, gp, st);
+  return run<MixSep64>(A, gp, st);
 }
 
 }  // namespace tsbts

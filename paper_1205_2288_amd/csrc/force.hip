@@ -124,7 +124,7 @@ __global__ __launch_bounds__(kWG) void k_force(ForceArgs A) {
   const int jt0 = slice * A.plan.tiles_per_slice;
   const int jt1 = min(jt0 + A.plan.tiles_per_slice, A.n_jtiles);
   const int64_t P = A.npad;
-  const F eps2 = sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2);
+  const F eps2 = in_vector(sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2));
 
   typename V::I I[IPL];
   int q[IPL];
@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kWG) void k_force_scalar(ForceArgs A) {
   if (slice >= A.plan.n_slices) return;
   const int jt0 = slice * A.plan.tiles_per_slice;
   const int jt1 = min(jt0 + A.plan.tiles_per_slice, A.n_jtiles);
-  const F eps2 = sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2);
+  const F eps2 = in_vector(sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2));
   const int lane = static_cast<int>(threadIdx.x) & 63;
   const int w = SH == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q = SH == 1 ? itile * kWG + static_cast<int>(threadIdx.x) : itile * 64 + lane;
@@ -272,7 +272,7 @@ __device__ __forceinline__ void small_tile_sums(const ForceArgs &A, const typena
   using F = typename V::F;
   __shared__ F red[kSmallAct][4][kWG / 64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const F eps2 = sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2);
+  const F eps2 = in_vector(sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2));
   for (int q0 = 0; q0 < A.n_act; q0 += kSmallGroup) {
     F x[4 * kSmallGroup];
 #pragma unroll

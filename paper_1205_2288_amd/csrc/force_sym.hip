@@ -13,10 +13,16 @@
 namespace tsbts {
 namespace {
 
-// columns per LDS transposition and values per column: with the potential 8 columns of
-// (x, y, z, potential), without it 16 columns of (x, y, z) (same LDS footprint per wave)
-template <int POT> struct FCols {
-  static constexpr int kBlock = POT ? 8 : 16;
+// Columns per LDS transposition, columns per meeting of the four waves, and values per
+// column, (x, y, z) and the potential, by type: the LDS holds the same bytes in float64.
+// Blocks of 16 columns unrolled by 8 and a barrier for each took 114 vector registers
+// without the potential, but 169 and two waves per SIMD with it, in blocks of 8.  With the
+// potential unrolled by 4 and one barrier per 64 columns: 134, and 6.02 -> 4.79 ms for all
+// of N = 131072.  Without it that form is the slower one (4.52 against 4.41 ms).
+template <class F, int POT> struct FCols {
+  static constexpr int kBlock = (POT ? 8 : 16) / (sizeof(F) / 4);
+  static constexpr int kMeet = POT ? 64 : kBlock;
+  static constexpr int kUnroll = sizeof(F) == 4 && !POT ? 8 : 4;
   static constexpr int kNV = POT ? 4 : 3;
 };
 
@@ -98,12 +104,10 @@ __device__ __forceinline__ void force_block(const ForceSymArgs &A,
                                             typename V::F (&a)[kSymRows][4],
                                             typename V::F *L, int lane) {
   using F = typename V::F;
-  constexpr int NV = FCols<POT>::kNV;
-  // columns per transposition (float64: half, same LDS bytes); the float64 column records
-  // of an 8-column batch would not fit the scalar registers, so those batch by 4
-  constexpr int BLK = sizeof(F) == 4 ? FCols<POT>::kBlock : FCols<POT>::kBlock / 2;
-  constexpr int UNR = sizeof(F) == 4 ? 8 : 4;
-  const F eps2 = sizeof(F) == 4 ? static_cast<F>(A.eps2) : static_cast<F>(A.eps2_64);
+  constexpr int NV = FCols<F, POT>::kNV;
+  constexpr int BLK = FCols<F, POT>::kBlock;
+  constexpr int UNR = FCols<F, POT>::kUnroll;
+  const F eps2 = in_vector(sizeof(F) == 4 ? static_cast<F>(A.eps2) : static_cast<F>(A.eps2_64));
 #pragma unroll UNR
   for (int c = 0; c < BLK; ++c) {
     const int64_t j = jb + c;
@@ -130,14 +134,14 @@ __global__ __launch_bounds__(kWG) void k_force_sym(ForceSymArgs A0,
                                                    typename V::F *__restrict__ col_part,
                                                    double *__restrict__ row_part) {
   using F = typename V::F;
-  // float64: half the columns per transposition (same LDS bytes)
-  constexpr int BLK = sizeof(F) == 4 ? FCols<POT>::kBlock : FCols<POT>::kBlock / 2;
-  constexpr int NV = FCols<POT>::kNV;
+  constexpr int BLK = FCols<F, POT>::kBlock;
+  constexpr int NV = FCols<F, POT>::kNV;
+  constexpr int MEET = FCols<F, POT>::kMeet;
   __shared__ F lds[kWG / 64][BLK * kSymLdsStride * NV];
   ForceSymArgs A = A0;
   A.p32 = p32;
   A.p64 = p64;
-  __shared__ F xs[2][kSymWaves][NV][BLK];
+  __shared__ F xs[2][kSymWaves][NV][MEET];
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int4 it = A.plan.items[blockIdx.x];  // one work item per workgroup
@@ -145,6 +149,7 @@ __global__ __launch_bounds__(kWG) void k_force_sym(ForceSymArgs A0,
   F *cpart = col_part + static_cast<int64_t>(it.x) * 4 * A.npad;
   double *rp = row_part + static_cast<int64_t>(it.w) * 4 * A.plan.npad_rows;
   int buf = 0;
+  const auto add = [](F x, F y) { return x + y; };
   SymSub sg;
   for (int sub = 0; sym_sub(A.plan, it, sub, sg); ++sub) {
     const int64_t row0 = sg.grow0 + static_cast<int64_t>(wv) * kSymWaveRows;
@@ -171,6 +176,7 @@ __global__ __launch_bounds__(kWG) void k_force_sym(ForceSymArgs A0,
       for (int r = 0; r < kSymRows; ++r)
 #pragma unroll
         for (int v = 0; v < 4; ++v) a[r][v] = F(0);
+#pragma unroll 1
       for (int64_t jb = jt; jb < jt + 64; jb += BLK) {
         if (rows_pad || jb < row0 + kSymWaveRows || jb + BLK > A.n)
           force_block<V, POT, 1>(A, rows, mr, k, jb, a, L, lane);
@@ -179,14 +185,21 @@ __global__ __launch_bounds__(kWG) void k_force_sym(ForceSymArgs A0,
         wave_lds_sync();
         F cs[NV];
         sym_col_sums<BLK, NV>(L, lane, cs);
-        sym_group_store<BLK, NV>(xs, buf, wv, lane, cs, cpart + jb, A.npad,
-                                 [](F x, F y) { return x + y; }, sub > 0);
+        sym_keep<BLK, NV>(xs[buf], wv, lane, static_cast<int>(jb - jt) % MEET, cs);
+        if constexpr (MEET == BLK) {
+          sym_group_store<NV>(xs[buf], wv, lane, cpart + jb, A.npad, add, sub > 0);
+          buf ^= 1;
+        }
         wave_lds_sync();
       }
 #pragma unroll
       for (int r = 0; r < kSymRows; ++r)
 #pragma unroll
         for (int v = 0; v < 4; ++v) tot[r][v] += static_cast<double>(a[r][v]);
+      if constexpr (MEET == 64) {
+        sym_group_store<NV>(xs[buf], wv, lane, cpart + jt, A.npad, add, sub > 0);
+        buf ^= 1;
+      }
     }
 #pragma unroll
     for (int r = 0; r < kSymRows; ++r)

@@ -110,6 +110,15 @@ __device__ __forceinline__ int xcd_linear(int bid, int nblk) {
   return (bid & 7) * (nblk >> 3) + (bid >> 3);
 }
 
+// A wave-uniform value as a vector operand: a float32 instruction with a scalar register
+// among its operands issues in 4.4 cycles, with vector registers only in 2.7 (measured at
+// 8 waves per SIMD; float64 ones take 4.4 either way).
+template <class T>
+__device__ __forceinline__ T in_vector(T x) {
+  asm("" : "+v"(x));
+  return x;
+}
+
 __device__ __forceinline__ float rsq_f32(float x) { return __builtin_amdgcn_rsqf(x); }
 __device__ __forceinline__ double rsq_f64_approx(double x) { return __builtin_amdgcn_rsq(x); }
 
@@ -596,9 +605,10 @@ bool force_sym_applies(const tsbts_ctx *c, int64_t n_act);
 hipError_t launch_force_sym(tsbts_ctx *c, const SymPlan &plan, const int32_t *idx, int n_act,
                             double *acc, double *pot, hipStream_t st,
                             const CorrectArgs *corr, const SymSet *set = nullptr);
-// Symmetric all-targets force adjoint (backward_sym.hip), after the seeds are ordered.
+// Symmetric all-targets force adjoint (backward_sym.hip), after the seeds are ordered (gp:
+// whether the potential has any).
 bool bwd_sym_applies(const tsbts_ctx *c, int64_t n_act);
-hipError_t launch_bwd_sym(tsbts_ctx *c, const SymPlan &plan, double *gr, double *gm,
+hipError_t launch_bwd_sym(tsbts_ctx *c, const SymPlan &plan, bool gp, double *gr, double *gm,
                           hipStream_t st);
 // Adjoints of the passes of an era (hist_adjoint.hip).
 hipError_t launch_interp_adjoint(tsbts_ctx *c, double t_block, double *pbar, double *hbar,

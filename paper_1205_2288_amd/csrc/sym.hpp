@@ -92,31 +92,34 @@ __device__ __forceinline__ bool sym_sub(const SymPlan &plan, const int4 &it, int
   return true;
 }
 
-// The four waves' column values of one transposition block (lanes < BLK of each wave hold
-// those of column jb + lane) are combined through LDS in wave order by the first wave and
-// stored to dst[v * stride + lane].  xs is double-buffered: one workgroup barrier per block
-// keeps a wave from overwriting a buffer the first wave still reads.
+// The four waves' column values of COLS columns meet in LDS, where every wave puts those of
+// a transposition block (lanes < BLK hold column col + lane) as it has them; after one
+// barrier wave v adds value v over the waves in wave order (and further values in turn)
+// and stores it to dst[v * stride + lane].  xs is double-buffered: a wave can only reach
+// the buffer again past the next barrier.
 // With acc, the result is combined (op) with the value already at dst: the column
 // partial of an earlier row group of the same band, written by this same lane.
-template <int BLK, int NV, class T, class Op>
-__device__ __forceinline__ void sym_group_store(T (&xs)[2][kSymWaves][NV][BLK], int &buf,
-                                                int wv, int lane, const T (&cs)[NV],
-                                                T *dst, int64_t stride, Op op, bool acc) {
+template <int BLK, int NV, int COLS, class T>
+__device__ __forceinline__ void sym_keep(T (&xs)[kSymWaves][NV][COLS], int wv, int lane,
+                                         int col, const T (&cs)[NV]) {
   if (lane < BLK) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) xs[buf][wv][v][lane] = cs[v];
+    for (int v = 0; v < NV; ++v) xs[wv][v][col + lane] = cs[v];
   }
+}
+template <int NV, int COLS, class T, class Op>
+__device__ __forceinline__ void sym_group_store(const T (&xs)[kSymWaves][NV][COLS], int wv,
+                                                int lane, T *dst, int64_t stride, Op op,
+                                                bool acc) {
   __syncthreads();
-  if (wv == 0 && lane < BLK) {
+  if (COLS < 64 && lane >= COLS) return;
+  for (int v = wv; v < NV; v += kSymWaves) {
+    T t = xs[0][v][lane];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      T t = xs[buf][0][v][lane];
-#pragma unroll
-      for (int w = 1; w < kSymWaves; ++w) t = op(t, xs[buf][w][v][lane]);
-      dst[v * stride + lane] = acc ? op(dst[v * stride + lane], t) : t;
-    }
+    for (int w = 1; w < kSymWaves; ++w) t = op(t, xs[w][v][lane]);
+    T *d = dst + v * stride + lane;
+    *d = acc ? op(*d, t) : t;
   }
-  buf ^= 1;
 }
 
 // Make the LDS writes of this wave visible to its other lanes and keep the compiler from
@@ -142,6 +145,7 @@ __device__ __forceinline__ void sym_col_sums(const T *L, int lane, T out[NV]) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) out[v] += e[v];
   }
+  // (shuffles: the LDS has time here, the vector units have none)
 #pragma unroll
   for (int off = BLK; off < 64; off <<= 1) {
 #pragma unroll

@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kWG) void k_timestep_sym(StepSymArgs A0,
   A.p64 = p64;
   A.v64 = v64;
   __shared__ F lds[kWG / 64][kSymBlock * kSymLdsStride * 2];
-  __shared__ F xs[2][kSymWaves][2][kSymBlock];
+  __shared__ F xs[2][kSymWaves][2][64];
   // the wave index is uniform over the wave: say so, so that the row tile and the column
   // index are scalar and the column records arrive through scalar loads
   const int lane = threadIdx.x & 63;
@@ -121,32 +121,35 @@ __global__ __launch_bounds__(kWG) void k_timestep_sym(StepSymArgs A0,
       swmin[r] = inf_of<F>();
     }
     const bool rows_pad = row0 + kSymWaveRows > A.n;
-    for (int64_t jb = sg.j0; jb < it.z; jb += kSymBlock) {
-      if (rows_pad || jb < row0 + kSymWaveRows || jb + kSymBlock > A.n)
-        sym_block<V, 1>(A, rows, wr, er, k, jb, eps2, qmax, swmin, L, lane);
-      else
-        sym_block<V, 0>(A, rows, wr, er, k, jb, eps2, qmax, swmin, L, lane);
-      wave_lds_sync();
-      // column c = lane & 15 over the 16 lanes' entries of this lane's quarter, then the
-      // four quarters
-      const int c = lane & 15, quarter = lane >> 4;
-      F cq = F(0), cs = inf_of<F>();
+    for (int64_t jt = sg.j0; jt < it.z; jt += 64) {
+#pragma unroll 1
+      for (int64_t jb = jt; jb < jt + 64; jb += kSymBlock) {
+        if (rows_pad || jb < row0 + kSymWaveRows || jb + kSymBlock > A.n)
+          sym_block<V, 1>(A, rows, wr, er, k, jb, eps2, qmax, swmin, L, lane);
+        else
+          sym_block<V, 0>(A, rows, wr, er, k, jb, eps2, qmax, swmin, L, lane);
+        wave_lds_sync();
+        // column c = lane & 15 over the 16 lanes' entries of this lane's quarter, then the
+        // four quarters
+        const int c = lane & 15, quarter = lane >> 4;
+        F cq = F(0), cs = inf_of<F>();
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int e = (c * kSymLdsStride + quarter * 16 + i) * 2;
-        cq = fmax(cq, L[e]);
-        cs = fmin(cs, L[e + 1]);
+        for (int i = 0; i < 16; ++i) {
+          const int e = (c * kSymLdsStride + quarter * 16 + i) * 2;
+          cq = fmax(cq, L[e]);
+          cs = fmin(cs, L[e + 1]);
+        }
+        const auto larger = [](F x, F y) { return fmax(x, y); };
+        const F both[2] = {lane_pair<32>(lane_pair<16>(cq, larger), larger),
+                           lane_pair<32>(lane_pair<16>(-cs, larger), larger)};
+        sym_keep<kSymBlock, 2>(xs[buf], wv, lane, static_cast<int>(jb - jt), both);
+        wave_lds_sync();
       }
-      cq = fmax(cq, __shfl_xor(cq, 16, 64));
-      cs = fmin(cs, __shfl_xor(cs, 16, 64));
-      cq = fmax(cq, __shfl_xor(cq, 32, 64));
-      cs = fmin(cs, __shfl_xor(cs, 32, 64));
-      // over the four waves (and the band's row groups): maxima of the first value,
-      // minima of the second
-      const F both[2] = {cq, -cs};
-      sym_group_store<kSymBlock, 2>(xs, buf, wv, lane, both, colq + jb, A.npad,
-                                    [](F x, F y) { return fmax(x, y); }, sub > 0);
-      wave_lds_sync();
+      // over the four waves (and the band's row groups): maxima of both values, the second
+      // the negated minimum
+      sym_group_store<2>(xs[buf], wv, lane, colq + jt, A.npad,
+                         [](F x, F y) { return fmax(x, y); }, sub > 0);
+      buf ^= 1;
     }
 #pragma unroll
     for (int r = 0; r < kSymRows; ++r) {
