@@ -52,9 +52,10 @@ __device__ __forceinline__ TargetState load_target(const CorrectArgs &p, int64_t
 // Target q (particle g, inputs s) with new acceleration an: r <- predicted position,
 // v <- v + (a + an) h / 2, a <- an, t_last <- t_block; append the record when recording.
 // Writes only the bound state, the float64 / float32 velocity planes and the record of g,
-// none of which a force kernel reads.
+// none of which a force kernel reads.  The new velocity also goes to vnew when given.
 __device__ __forceinline__ void correct_target(const CorrectArgs &p, int q, int64_t g,
-                                               const double an[3], const TargetState &s) {
+                                               const double an[3], const TargetState &s,
+                                               double *vnew = nullptr) {
   const int64_t n = p.n, P = p.npad;
   const double h = p.tb - s.tl;
   double st[9];
@@ -66,6 +67,7 @@ __device__ __forceinline__ void correct_target(const CorrectArgs &p, int q, int6
     p.v[c * n + g] = vn;
     p.a[c * n + g] = an[c];
     p.v64[c * P + g] = vn;
+    if (vnew) vnew[c] = vn;
     if (p.p32) p.p32[(P32_VX + c) * P + g] = static_cast<float>(vn);
     st[c] = rn;
     st[c + 3] = vn;

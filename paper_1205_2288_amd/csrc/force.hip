@@ -51,6 +51,7 @@ struct ForceArgs {
   int n_act;
   SplitPlan plan;
   int n_jtiles;
+  int used_tiles;  // without those of padding alone (small active sets)
   float eps2f;
   double eps2;
   double *part;  // [S][4][n_act] raw sums when S > 1
@@ -61,10 +62,13 @@ struct ForceArgs {
   int scalar_j;  // j-particles through scalar loads (k_force_scalar)
   int chunk;     // j-particles per split unit of k_force_scalar
   ShareShape share;  // the split when its waves share the targets
+  uint32_t *share_done;  // ... and its finished-workgroup counts
   int correct;   // apply the corrector to each target as its force is finished
   CorrectArgs corr;
-  uint32_t *done;   // finished-workgroup count of the small-set kernels
-  int fuse_reduce;  // the small-set kernel's last workgroup reduces the partials
+  // the small-set kernels' last workgroup, or that of each tile of 64 targets (share),
+  // reduces the partials; done: finished-workgroup count, or one per tile
+  uint32_t *done;
+  int fuse_reduce;
   CritArgs crit;    // ... and then takes the criterion (k_force_small_pred)
   // Sources of k_force_scalar (null: the predicted arrays above): planes of stride snpad.
   // self = 0 when they exclude the targets (no self pair to skip).
@@ -82,7 +86,8 @@ struct ForceArgs {
 template <class V, int NEWTON>
 __device__ __forceinline__ void finish(const ForceArgs &A, int q, int64_t g, double sx,
                                        double sy, double sz, double sp,
-                                       const TargetState *ts = nullptr) {
+                                       const TargetState *ts = nullptr,
+                                       double *vnew = nullptr) {
   const double k = Scale<V, NEWTON>::kAcc;
   double an[3] = {k * sx, k * sy, k * sz};
   double pn = -sp;
@@ -95,7 +100,7 @@ __device__ __forceinline__ void finish(const ForceArgs &A, int q, int64_t g, dou
   A.acc[A.n_act + q] = an[1];
   A.acc[2 * A.n_act + q] = an[2];
   if (A.pot) A.pot[q] = pn;
-  if (A.correct) correct_target(A.corr, q, g, an, ts ? *ts : load_target(A.corr, g));
+  if (A.correct) correct_target(A.corr, q, g, an, ts ? *ts : load_target(A.corr, g), vnew);
 }
 
 template <class V, int NEWTON, int MASK, int POT, int IPL, class F>
@@ -196,6 +201,32 @@ __device__ __forceinline__ void scalar_tile(const ForceArgs &A, const typename V
   }
 }
 
+// The reduction of 64 targets' partials by the workgroup that finished their tile last:
+// wave c adds component c, one target per lane, in slice order as k_force_reduce does;
+// wave 0 then finishes the targets, its corrector's inputs read with the partials.
+template <class V, int NEWTON>
+__device__ __forceinline__ void share_reduce_last(const ForceArgs &A, int q, int g, int w,
+                                                  int lane) {
+  static_assert(kShare == 4, "a wave per component");
+  __shared__ double sums[4][64];
+  const int S = A.plan.n_slices;
+  const int64_t stride = 4 * static_cast<int64_t>(A.n_act);
+  const double *in = A.part + w * static_cast<int64_t>(A.n_act) + min(q, A.n_act - 1);
+  TargetState ts{};
+  if (w == 0 && A.correct) ts = load_target(A.corr, g);
+  double x[kShareFuse];
+#pragma unroll
+  for (int s = 0; s < kShareFuse; ++s) x[s] = load_partial(in + min(s, S - 1) * stride);
+  double t = 0.0;
+#pragma unroll
+  for (int s = 0; s < kShareFuse; ++s)
+    if (s < S) t += x[s];
+  sums[w][lane] = t;
+  __syncthreads();
+  if (w == 0 && q < A.n_act)
+    finish<V, NEWTON>(A, q, g, sums[0][lane], sums[1][lane], sums[2][lane], sums[3][lane], &ts);
+}
+
 // Split units of SH * CH j-particles (A.n_jtiles counts them here): with SH = 1 a target
 // per lane of the workgroup, with SH = kShare a target per lane of every wave, wave w
 // taking part w of each unit; the waves' float64 sums are then added in wave order.
@@ -235,6 +266,17 @@ __global__ __launch_bounds__(kWG) void k_force_scalar(ForceArgs A) {
     red[w][2][lane] = sz;
     red[w][3][lane] = sp;
     __syncthreads();
+    if (A.fuse_reduce) {
+      // wave c: component c of the waves, in wave order
+      double x = red[0][w][lane];
+#pragma unroll
+      for (int u = 1; u < SH; ++u) x += red[u][w][lane];
+      if (q < A.n_act)
+        store_partial(&A.part[(static_cast<int64_t>(slice) * 4 + w) * A.n_act + q], x);
+      if (last_workgroup_partials(A.done + itile, A.plan.n_slices))
+        share_reduce_last<V, NEWTON>(A, q, g, w, lane);
+      return;
+    }
     if (w > 0) return;
 #pragma unroll
     for (int u = 1; u < SH; ++u) {
@@ -262,13 +304,14 @@ __global__ __launch_bounds__(kWG) void k_force_scalar(ForceArgs A) {
 // butterfly per value), then over the 4 waves in a fixed order into one float64 partial
 // per tile and target.  Keeps every lane busy where an i-tile would leave all but n_act
 // lanes idle.  When the partials are few (fuse_reduce) the launch's last workgroup adds
-// them and finishes the targets (small_reduce_last) instead of a second kernel.
+// them and finishes the targets (small_reduce_last) instead of a second kernel.  The sums
+// of a launch's only workgroup stay in LDS (one).
 constexpr int kSmallGroup = 8;
 
 template <class V, int NEWTON>
 __device__ __forceinline__ void small_tile_sums(const ForceArgs &A, const typename V::I *si,
                                                 const int *sg, const typename V::J &J,
-                                                int64_t j, int tile) {
+                                                int64_t j, int tile, double *one = nullptr) {
   using F = typename V::F;
   __shared__ F red[kSmallAct][4][kWG / 64];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -296,7 +339,10 @@ __device__ __forceinline__ void small_tile_sums(const ForceArgs &A, const typena
     double s = 0.0;
 #pragma unroll
     for (int ww = 0; ww < kWG / 64; ++ww) s += static_cast<double>(red[q][c][ww]);
-    store_partial(&A.part[(static_cast<int64_t>(tile) * 4 + c) * A.n_act + q], s);
+    if (one)
+      one[c * A.n_act + q] = s;
+    else
+      store_partial(&A.part[(static_cast<int64_t>(tile) * 4 + c) * A.n_act + q], s);
   }
 }
 
@@ -342,24 +388,53 @@ __device__ __forceinline__ void small_reduce_last(const ForceArgs &A, const int 
 // and min are exact, so dtc is what the criterion kernels give bit for bit.  The targets'
 // corrected velocities were stored by this workgroup; every other particle's predicted
 // record was stored before its workgroup counted itself in, so last_workgroup made it
-// visible.
+// visible.  ONE: this workgroup is the only one, each thread's particle is `own` (as
+// predicted) and the targets' positions and corrected velocities are si and tv in LDS.
 constexpr int kCritGroup = 8;
 constexpr int kCritBatch = 4;
 
-template <class V>
-__device__ __forceinline__ void small_criterion_last(const ForceArgs &A, const int *sg) {
+template <class J>
+__device__ __forceinline__ void set_velocity(J &r, const double *v) {
+  if constexpr (std::is_same<J, StepRec<Fp64>::J>::value) {
+    r.vx = v[0];
+    r.vy = v[1];
+    r.vz = v[2];
+  } else {
+    r.v.x = static_cast<float>(v[0]);
+    r.v.y = static_cast<float>(v[1]);
+    r.v.z = static_cast<float>(v[2]);
+  }
+}
+
+template <class V, bool ONE>
+__device__ __forceinline__ void small_criterion_last(const ForceArgs &A, const int *sg,
+                                                     const typename V::I *si,
+                                                     const double (*tv)[3],
+                                                     typename StepRec<V>::J own) {
   using F = typename V::F;
   using SR = StepRec<V>;
   constexpr int G = kCritGroup;
+  constexpr int kBatch = ONE ? 1 : kCritBatch;
   __shared__ typename SR::I ti[kSmallAct];
   __shared__ F red[kSmallAct][2][kWG / 64];
   const CritArgs &C = A.crit;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   __syncthreads();
-  if (tid < A.n_act) ti[tid] = load_iv<V>(C, sg[tid]);
+  if constexpr (ONE) {
+    if (tid < A.n_act) {
+      ti[tid].p = si[tid];
+      ti[tid].vx = static_cast<decltype(ti[tid].vx)>(tv[tid][0]);
+      ti[tid].vy = static_cast<decltype(ti[tid].vy)>(tv[tid][1]);
+      ti[tid].vz = static_cast<decltype(ti[tid].vz)>(tv[tid][2]);
+    }
+    for (int q = 0; q < A.n_act; ++q)
+      if (sg[q] == tid) set_velocity(own, tv[q]);
+  } else if (tid < A.n_act) {
+    ti[tid] = load_iv<V>(C, sg[tid]);
+  }
   __syncthreads();
   const F eps2 = static_cast<F>(C.eps2);
-  const int n_tiles = static_cast<int>(C.npad / kTJ);
+  const int n_tiles = ONE ? 1 : static_cast<int>((C.n + kTJ - 1) / kTJ);
   const F inf = sizeof(F) == 4 ? static_cast<F>(__builtin_inff()) : static_cast<F>(__builtin_inf());
   for (int q0 = 0; q0 < A.n_act; q0 += G) {
     F qm[G], sm[G];
@@ -368,13 +443,14 @@ __device__ __forceinline__ void small_criterion_last(const ForceArgs &A, const i
       qm[u] = F(0);
       sm[u] = inf;
     }
-    for (int jt = 0; jt < n_tiles; jt += kCritBatch) {
-      typename SR::J J[kCritBatch];
+    for (int jt = 0; jt < n_tiles; jt += kBatch) {
+      typename SR::J J[kBatch];
 #pragma unroll
-      for (int b = 0; b < kCritBatch; ++b)
-        if (jt + b < n_tiles) J[b] = load_jv<V>(C, static_cast<int64_t>(jt + b) * kTJ + tid);
+      for (int b = 0; b < kBatch; ++b)
+        if (jt + b < n_tiles)
+          J[b] = ONE ? own : load_jv<V>(C, static_cast<int64_t>(jt + b) * kTJ + tid);
 #pragma unroll
-      for (int b = 0; b < kCritBatch; ++b) {
+      for (int b = 0; b < kBatch; ++b) {
         if (jt + b >= n_tiles) break;
         const int64_t j = static_cast<int64_t>(jt + b) * kTJ + tid;
 #pragma unroll
@@ -429,7 +505,8 @@ __global__ __launch_bounds__(kWG) void k_force_small(ForceArgs A) {
   }
   __syncthreads();
   small_tile_sums<V, NEWTON>(A, si, sg, J, j, tile);
-  if (A.fuse_reduce && last_workgroup_partials(A.done)) small_reduce_last<V, NEWTON>(A, sg);
+  if (A.fuse_reduce && last_workgroup_partials(A.done, gridDim.x))
+    small_reduce_last<V, NEWTON>(A, sg);
 }
 
 // Source record of a policy built from a particle's predicted position and mass: the
@@ -457,6 +534,24 @@ __device__ __forceinline__ typename V::J j_from_state(double x, double y, double
     r.a = make_float4(hx, hy, hz, static_cast<float>(m) * ms);
     r.b = make_float4(lx, ly, lz, static_cast<float>(ff_weight(m)));
   }
+  return r;
+}
+
+// The criterion's source record likewise (p: j_from_state's record), what load_jv reads
+// back, and its velocity after a correction.
+template <class V>
+__device__ __forceinline__ typename StepRec<V>::J jv_from_state(const typename V::J &p,
+                                                                const double st[6], double m,
+                                                                double eps2) {
+  typename StepRec<V>::J r;
+  r.p = p;
+  const double w = ff_weight(m);
+  if constexpr (sizeof(typename V::F) == 4) {
+    r.v.w = eps2 > 0.0 ? static_cast<float>(eps2 * w) : 0.0f;
+  } else {
+    r.w = w;
+  }
+  set_velocity(r, st + 3);
   return r;
 }
 
@@ -512,26 +607,45 @@ __global__ __launch_bounds__(kWG) void k_force_small_pred(ForceArgs A, PredictAr
     for (int c = 0; c < 3; ++c) ts.rn[c] = st[c];
     si[tid] = i_from_state<V>(st[0], st[1], st[2]);
   }
+  __shared__ double one[4 * kSmallAct], tv[kSmallAct][3];
+  const bool alone = gridDim.x == 1;
   typename V::J J;
+  typename StepRec<V>::J Jc;
   if (j < Pr.n) {
     double st[6];
     predict_state(Pr, j, true, st);
     const double m = Pr.m[j];
     store_particle(Pr.o, j, st[0], st[1], st[2], st[3], st[4], st[5], m);
     J = j_from_state<V>(st[0], st[1], st[2], m, ms);
+    Jc = jv_from_state<V>(J, st, m, Pr.o.eps2);
   } else {
+    const double rest[6] = {kFar, kFar, kFar, 0.0, 0.0, 0.0};
     store_pad(Pr.o, j);
     J = j_from_state<V>(kFar, kFar, kFar, 0.0, ms);
+    Jc = jv_from_state<V>(J, rest, 0.0, Pr.o.eps2);
   }
+  const int64_t width = static_cast<int64_t>(gridDim.x) * kTJ;
+  for (int64_t jp = j + width; jp < A.npad; jp += width)
+    store_pad(Pr.o, jp);
   if (blockIdx.x == 0) store_inline_idx(in, tid);
   __syncthreads();
-  small_tile_sums<V, NEWTON>(A, si, sg, J, j, tile);
+  small_tile_sums<V, NEWTON>(A, si, sg, J, j, tile, alone ? one : nullptr);
+  if (alone) {
+    // nothing passes through memory: a block step of up to 16 targets on N = 256 takes
+    // 17.1 instead of 22.4 us with its criterion (float64)
+    __syncthreads();
+    if (tid < A.n_act)
+      finish<V, NEWTON>(A, tid, sg[tid], one[tid], one[A.n_act + tid], one[2 * A.n_act + tid],
+                        one[3 * A.n_act + tid], &ts, tv[tid]);
+    if (A.crit.on) small_criterion_last<V, true>(A, sg, si, tv, Jc);
+    return;
+  }
   // (the criterion also reads the planes the other workgroups stored)
   if (!A.fuse_reduce ||
-      !(A.crit.on ? last_workgroup(A.done) : last_workgroup_partials(A.done)))
+      !(A.crit.on ? last_workgroup(A.done) : last_workgroup_partials(A.done, gridDim.x)))
     return;
   small_reduce_last<V, NEWTON>(A, sg, &ts);
-  if (A.crit.on) small_criterion_last<V>(A, sg);
+  if (A.crit.on) small_criterion_last<V, false>(A, sg, si, tv, Jc);
 }
 
 // Add the slices' partials in slice order and finish (scale, sign).
@@ -636,6 +750,8 @@ hipError_t run_scalar(ForceArgs &A, hipStream_t st) {
     chunk = A.share.chunk;
     A.n_jtiles = A.share.n_units;
     A.plan = A.share.plan;
+    A.fuse_reduce = A.plan.n_slices > 1 && A.plan.n_slices <= kShareFuse ? 1 : 0;
+    A.done = A.share_done;
   } else {
     A.n_jtiles = static_cast<int>(A.snpad / chunk);
     A.plan = plan_split(A.n_act, 1, A.n_jtiles, A.blocks);
@@ -657,7 +773,7 @@ hipError_t run_scalar(ForceArgs &A, hipStream_t st) {
                : k_force_scalar<V, NEWTON, 0, kChunkSmall, 1>);
   else
     launch(pot ? k_force_scalar<V, NEWTON, 1, kTJ, 1> : k_force_scalar<V, NEWTON, 0, kTJ, 1>);
-  return launch_reduce<V, NEWTON>(A, st);
+  return A.fuse_reduce ? hipGetLastError() : launch_reduce<V, NEWTON>(A, st);
 }
 
 template <class V, int NEWTON, int IPL>
@@ -673,6 +789,7 @@ hipError_t run(ForceArgs &A, hipStream_t st) {
 template <class V, int NEWTON>
 hipError_t run_small(ForceArgs &A, hipStream_t st, const PredictArgs *pred = nullptr,
                      const InlineIdx *in = nullptr) {
+  A.n_jtiles = A.used_tiles;
   A.plan.n_itiles = 1;
   A.plan.n_slices = A.n_jtiles;
   A.plan.tiles_per_slice = 1;
@@ -725,7 +842,7 @@ ShareShape share_shape(const tsbts_ctx *c, int n_act, int chunk) {
   if (!chunk)
     chunk = itiles * (c->npad / (kShare * kChunkSmall)) < 512 ? kChunkTiny : kChunkSmall;
   s.chunk = chunk;
-  s.n_units = static_cast<int>((c->npad + kShare * chunk - 1) / (kShare * chunk));
+  s.n_units = static_cast<int>((c->n + kShare * chunk - 1) / (kShare * chunk));
   // about 2048 workgroups, and few slices for the rows reduction: at most half of what it
   // takes unless each would hold several units
   const int64_t cap = s.n_units >= 2 * kRowsFewSlices ? kRowsFewSlices : kRowsFewSlices / 2;
@@ -798,6 +915,7 @@ hipError_t launch_force_gather(tsbts_ctx *c, const int32_t *idx, int n_act, doub
   A.idx = idx;
   A.n_act = n_act;
   A.n_jtiles = static_cast<int>(c->npad / kTJ);
+  A.used_tiles = used_tiles(c);
   A.eps2f = static_cast<float>(c->eps * c->eps);
   A.eps2 = c->eps * c->eps;
   A.part = part;
@@ -808,6 +926,7 @@ hipError_t launch_force_gather(tsbts_ctx *c, const int32_t *idx, int n_act, doub
   A.scalar_j = force_scalar_j(c) ? 1 : 0;
   A.chunk = scalar_chunk(c, n_act, 1);
   A.share = share_force(c, n_act);
+  A.share_done = share_done(c, 0);
   A.done = c->done;
   A.fuse_reduce = 0;
   if (src) {
@@ -850,7 +969,7 @@ int small_act_limit(const tsbts_ctx *c) {
 }
 
 bool small_criterion_fused(const tsbts_ctx *c, int n_act) {
-  const int64_t tiles = c->npad / kTJ;
+  const int64_t tiles = used_tiles(c);
   const int groups = (n_act + kCritGroup - 1) / kCritGroup;
   return n_act <= small_act_limit(c) && fuse_small_reduce(static_cast<int>(tiles), 4 * n_act) &&
          tiles * groups <= kCritFuseTiles;
@@ -881,6 +1000,7 @@ hipError_t launch_force_predicted(tsbts_ctx *c, const int32_t *idx, int n_act, d
   A.idx = idx;
   A.n_act = n_act;
   A.n_jtiles = static_cast<int>(c->npad / kTJ);
+  A.used_tiles = used_tiles(c);
   A.eps2f = static_cast<float>(c->eps * c->eps);
   A.eps2 = c->eps * c->eps;
   A.part = c->part;

@@ -77,8 +77,9 @@ struct tsbts_ctx {
                                                       // range, [1] a repeated index
                                                       // (mapped pinned memory)
   int32_t *idx_seen = nullptr;  // [n] occurrence counters of the check
-  // finished-workgroup counts of the small-set force [0] and criterion [1] launches whose
-  // last workgroup reduces the partials (last_workgroup); zero between launches
+  // finished-workgroup counts of the launches whose last workgroup reduces the partials
+  // (last_workgroup), zero between launches: the small-set force [0] and criterion [1],
+  // then kShareTiles each for the tiles of 64 targets of the two (share_done)
   uint32_t *done = nullptr;
   // symmetric all-targets kernels: work items (int4) and partials
   void *sym_items = nullptr;
@@ -299,7 +300,7 @@ __device__ __forceinline__ bool last_workgroup(uint32_t *done) {
 }
 
 // The same where everything the last workgroup reads of the others' was written by
-// store_partial and is read by load_partial: those pass the caches that the XCDs do not
+// store_partial and is read by load_partial, of the `count` workgroups of `done`: those pass the caches that the XCDs do not
 // share (relaxed atomics of agent scope), so no cache is written back or emptied; every
 // thread waits until its stores have arrived before the workgroup is counted.  With the
 // register moves above instead of LDS shuffles, small calls on N = 4096 took (us, force /
@@ -311,13 +312,13 @@ __device__ __forceinline__ void store_partial(double *p, double x) {
 __device__ __forceinline__ double load_partial(const double *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ bool last_workgroup_partials(uint32_t *done) {
+__device__ __forceinline__ bool last_workgroup_partials(uint32_t *done, uint32_t count) {
   __shared__ uint32_t last;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (threadIdx.x == 0) {
     const uint32_t before = atomicAdd(done, 1u);
-    last = before + 1 == gridDim.x ? 1u : 0u;
+    last = before + 1 == count ? 1u : 0u;
     if (last) atomicExch(done, 0u);
   }
   __syncthreads();
@@ -358,6 +359,10 @@ __host__ __device__ inline bool fuse_small_reduce(int n_slices, int W) {
   const int parts = W <= kWG ? kWG / W : 1;
   return W <= kWG && n_slices <= kFuseSlices && (n_slices + parts - 1) / parts <= kFuseLoads;
 }
+
+// Tiles of kTJ that hold particles: the padding of the planes (to a multiple of kPad) can
+// be a whole tile, which the kernels of few targets leave out.
+inline int used_tiles(const tsbts_ctx *c) { return static_cast<int>((c->n + kTJ - 1) / kTJ); }
 
 // Active sets up to this size use the j-parallel pair kernels (one source per lane).
 constexpr int kSmallAct = 32;
@@ -431,12 +436,23 @@ inline int scalar_chunk(const tsbts_ctx *c, int n_act, int ipl) {
 // units of 4 x 64 would be fewer than 512 workgroups.
 constexpr int kShare = kWG / 64;
 constexpr int kShareMaxAct = 4096;
+constexpr int kShareTiles = kShareMaxAct / 64;
+// With at most kShareFuse slices (few particles) the workgroup that finishes a tile of 64
+// targets last reduces the tile's partials itself, in the order of the reduction kernels,
+// instead of a second launch.  Block steps of 33 to 256 targets, in us (separate, fused):
+// float64 N = 256 (4 slices) 26.8, 24.5, N = 500 (8) 29.3, 26.1; mixed N = 1000 (4, the
+// criterion separate) 32.5, 32.1, with its 16 slices fused too 38.5; N = 4096 (16 and 64
+// fused) 32.4, 40: more slices wait longer for the last one than a launch takes.
+constexpr int kShareFuse = 8;
 constexpr int kChunkTiny = 16;
 struct ShareShape {
   int chunk;       // j-particles per wave and unit; 0: not this form
   int n_units;     // units of kShare * chunk (the last one may pass the padding)
   SplitPlan plan;  // n_itiles counts 64 targets
 };
+inline uint32_t *share_done(const tsbts_ctx *c, int which) {
+  return c->done + 2 + which * kShareTiles;
+}
 ShareShape share_force(const tsbts_ctx *c, int n_act);
 ShareShape share_step(const tsbts_ctx *c, int n_act);
 // The criterion kernel likewise for large active sets (from 8192 targets, two targets per

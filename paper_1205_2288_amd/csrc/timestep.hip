@@ -35,8 +35,11 @@ struct StepArgs {
   int scalar_j;  // j-particles through scalar loads (k_timestep_scalar)
   int chunk;     // j-particles per split unit of k_timestep_scalar
   ShareShape share;  // the split when its waves share the targets
-  uint32_t *done;   // finished-workgroup count of k_timestep_small
-  int fuse_reduce;  // its last workgroup reduces the partials
+  uint32_t *share_done;  // ... and its finished-workgroup counts
+  // k_timestep_small's last workgroup, or that of each tile of 64 targets (share), reduces
+  // the partials; done: finished-workgroup count, or one per tile
+  uint32_t *done;
+  int fuse_reduce;
   // Sources of k_timestep_scalar (null s64: the predicted arrays above): sn particles,
   // planes of stride snpad; self = 0 when they exclude the targets.
   const float *s32 = nullptr;
@@ -187,6 +190,32 @@ __global__ __launch_bounds__(kWG) void k_timestep_scalar(StepArgs A) {
     red[w][0][lane] = qmax[0];
     red[w][1][lane] = swmin[0];
     __syncthreads();
+    if (A.fuse_reduce) {
+      // wave 0 stores the maxima over the waves, wave 1 the minima; in the tile's last
+      // workgroup waves 0 and 2 take the maxima, 1 and 3 the minima of half the slices
+      const auto pick = [&](double a, double b) { return w & 1 ? fmin(a, b) : fmax(a, b); };
+      const int64_t at = (w & 1) * static_cast<int64_t>(A.n_act) + min(q[0], A.n_act - 1);
+      if (w < 2 && q[0] < A.n_act) {
+        double x = static_cast<double>(red[0][w][lane]);
+#pragma unroll
+        for (int u = 1; u < SH; ++u) x = pick(x, static_cast<double>(red[u][w][lane]));
+        store_partial(&A.part[static_cast<int64_t>(slice) * 2 * A.n_act + at], x);
+      }
+      if (!last_workgroup_partials(A.done + itile, A.plan.n_slices)) return;
+      __shared__ double half[4][64];
+      const int S = A.plan.n_slices, H = (S + 1) / 2;
+      const int s1 = w < 2 ? H : S;
+      double x = w & 1 ? __builtin_inf() : 0.0;
+#pragma unroll 16
+      for (int s = w < 2 ? 0 : H; s < s1; ++s)
+        x = pick(x, load_partial(&A.part[static_cast<int64_t>(s) * 2 * A.n_act + at]));
+      half[w][lane] = x;
+      __syncthreads();
+      if (w == 0 && q[0] < A.n_act)
+        finish_target(A, q[0], fmax(half[0][lane], half[2][lane]),
+                      fmin(half[1][lane], half[3][lane]));
+      return;
+    }
     if (w > 0) return;
 #pragma unroll
     for (int u = 1; u < SH; ++u) {
@@ -265,7 +294,7 @@ __global__ __launch_bounds__(kWG) void k_timestep_small(StepArgs A) {
                  : fmin(s, static_cast<double>(red[q][c][ww]));
     store_partial(&A.part[(static_cast<int64_t>(tile) * 2 + c) * A.n_act + q], s);
   }
-  if (!A.fuse_reduce || !last_workgroup_partials(A.done)) return;
+  if (!A.fuse_reduce || !last_workgroup_partials(A.done, gridDim.x)) return;
   // the launch's last workgroup: a slice's partials form a row of W = 2 n_act values (the
   // maxima, then the minima); thread t combines value t % W over part t / W of the slices
   const int W = 2 * A.n_act, S = A.plan.n_slices, P = min(kWG / W, S);
@@ -353,6 +382,7 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_timestep_reduce_rows(StepAr
 template <class V>
 hipError_t run(StepArgs &A, hipStream_t st) {
   if (A.n_act <= kSmallAct) {
+    A.n_jtiles = static_cast<int>((A.n + kTJ - 1) / kTJ);  // without padding alone
     A.plan.n_itiles = 1;
     A.plan.n_slices = A.n_jtiles;
     A.plan.tiles_per_slice = 1;
@@ -372,6 +402,8 @@ hipError_t run(StepArgs &A, hipStream_t st) {
     if (A.share.chunk) {
       A.n_jtiles = A.share.n_units;
       A.plan = A.share.plan;
+      A.fuse_reduce = A.plan.n_slices > 1 && A.plan.n_slices <= kShareFuse ? 1 : 0;
+      A.done = A.share_done;
     } else {
       A.n_jtiles = static_cast<int>(A.snpad / A.chunk);
       A.plan = plan_split(A.n_act, A.ipl, A.n_jtiles, A.blocks);
@@ -388,6 +420,7 @@ hipError_t run(StepArgs &A, hipStream_t st) {
     else
       launch(A.chunk == kTJ ? k_timestep_scalar<V, 1, kTJ, 1>
                             : k_timestep_scalar<V, 1, kChunkSmall, 1>);
+    if (A.fuse_reduce) return hipGetLastError();
   } else {
     A.plan = plan_split(A.n_act, A.ipl, A.n_jtiles, A.blocks);
     if (A.ipl == 4)
@@ -432,6 +465,7 @@ StepArgs gather_args(tsbts_ctx *c, const int32_t *idx, int n_act, double eta, do
   A.blocks = criterion_blocks(c, n_act);
   A.ipl = criterion_targets_per_lane(c, n_act);
   A.share = share_step(c, n_act);
+  A.share_done = share_done(c, 1);
   A.scalar_j = A.share.chunk || criterion_scalar_j(c, n_act) ? 1 : 0;
   A.chunk = scalar_chunk(c, n_act, A.ipl);
   A.done = c->done + 1;

@@ -1,0 +1,67 @@
+"""Few particles: the launches that finish their own reduction and those of one workgroup.
+
+* block steps of up to 32 targets whose launch is a single workgroup (at most 256
+  particles, padding tiles left out) against the separate predictor, force and criterion
+  launches: the same run bit for bit, at particle counts around one and two tiles;
+* sets of 33 targets and more whose partials the last workgroup of each 64 targets adds
+  (at most 8 slices): force against the oracle, force and criterion unchanged over calls
+  (the workgroup counts return to zero) and in a captured graph's replays."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from workloads import plummer
+from gpu_util import rel_err_vec, summary, make_ctx, TOL
+from paper_1205_2288_amd import _lib as L
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("prec", ["fp64", "mixed"])
+@pytest.mark.parametrize("n", [40, 255, 256, 257, 513])
+def test_one_workgroup_block_steps(prec, n):
+    from paper_1205_2288_amd.driver import NativeTSBTS
+    r, v, m = plummer(n, 7200 + n, masses="loguniform")
+    out = []
+    for pol in (False, True):
+        sim = NativeTSBTS(r, v, m, 1 / 64, eta=0.1, passes=2, era=1 / 16, dt_max=1 / 64,
+                          precision=prec, predict_on_load=pol)
+        sim.run(1 / 8)
+        out.append((sim.stats["block_steps"], sim.stats["interactions"],
+                    sim.ctx.r.cpu().numpy().copy(), sim.ctx.v.cpu().numpy().copy()))
+        sim.close()
+    assert out[0][:2] == out[1][:2]
+    assert np.array_equal(out[0][2], out[1][2]) and np.array_equal(out[0][3], out[1][3])
+
+
+@pytest.mark.parametrize("prec,sep", [("fp64", "f64"), ("mixed", "f64"), ("mixed", "hilo")])
+@pytest.mark.parametrize("n,k", [(40, 33), (256, 64), (500, 65), (513, 513), (2000, 129)])
+def test_tile_reductions(prec, sep, n, k):
+    r, v, m = plummer(n, 7300 + n, masses="loguniform")
+    idx = np.random.default_rng(n).permutation(n)[:k].astype(np.int32)
+    ctx = make_ctx(n, 1 / 256, prec, sep)
+    ctx.bind(r, v, m)
+    ctx.predict(0.0)
+    acc = ctx.force(idx, 0.0)[0].cpu().numpy()
+    dtc = ctx.timestep(idx, 0.1).cpu().numpy()
+    e = summary(rel_err_vec(acc, oracle.force(r, m, 1 / 256, idx)[0]))
+    assert e["median"] <= TOL[prec]["median"] and e["max"] <= TOL[prec]["max"], e
+    d_idx = ctx.idx(idx)
+    a = torch.zeros((3, k), dtype=torch.float64, device="cuda")
+    d = torch.zeros(k, dtype=torch.float64, device="cuda")
+    stream = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        for _ in range(2):
+            L.tsbts_force(ctx.ctx, d_idx, 0.0, a, None)
+            L.tsbts_timestep(ctx.ctx, d_idx, 0.1, d)
+    for _ in range(3):
+        a.zero_()
+        d.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(a.cpu().numpy(), acc) and np.array_equal(d.cpu().numpy(), dtc)
+        assert np.array_equal(ctx.force(idx, 0.0)[0].cpu().numpy(), acc)
+    ctx.close()
