@@ -61,6 +61,41 @@ def tsbts_force(r, m, idx, ctx: Context):
     return TsbtsForce.apply(r, m, idx, ctx)
 
 
+class _State:
+    """r, v, a [3, n], t_last and dt [n] of a run as views of one buffer, `flat`: a
+    checkpoint, a copy back or a step's pre-step state is one copy of 11 n values (five
+    copies took 5 launches, which set the time of a run on few particles: 52 of the 131
+    launches of four block steps and their gradient were copies)."""
+
+    def __init__(self, ctx: Context, flat):
+        n = ctx.n
+        self.flat = flat
+        self.r, self.v, self.a = (flat[3 * n * c:3 * n * (c + 1)].view(3, n) for c in range(3))
+        self.t_last, self.dt = flat[9 * n:10 * n], flat[10 * n:]
+
+    def bind(self, ctx: Context, m):
+        ctx.bind(self.r, self.v, m, a=self.a, t_last=self.t_last, dt=self.dt)
+        return self
+
+    @classmethod
+    def start(cls, ctx: Context, r0, v0, m, dt):
+        """At rest in time at r0, v0 with steps dt, accelerations of the start positions."""
+        st = cls(ctx, torch.empty(11 * ctx.n, dtype=torch.float64, device=ctx.device))
+        st.r.copy_(r0.reshape(3, ctx.n))
+        st.v.copy_(v0.reshape(3, ctx.n))
+        st.t_last.zero_()
+        if isinstance(dt, float):
+            st.dt.fill_(dt)
+        else:
+            st.dt.copy_(dt.reshape(ctx.n))
+        return st.bind(ctx, m.clone())
+
+    @classmethod
+    def like(cls, ctx: Context, flat, m):
+        """A bound state of its own (its values come from a later copy to flat)."""
+        return cls(ctx, torch.empty_like(flat)).bind(ctx, m)
+
+
 class TsbtsLeapfrog(torch.autograd.Function):
     """(r_S, v_S) after `steps` shared leapfrog steps of size h, with era checkpoints."""
 
@@ -69,18 +104,15 @@ class TsbtsLeapfrog(torch.autograd.Function):
         n = ctx.n
         dev = ctx.device
         r0, v0, m = (x.detach().contiguous() for x in (r0, v0, m))
-        ctx.bind(r0.clone(), v0.clone(), m.clone(), t_last=torch.zeros(n, dtype=torch.float64,
-                                                                        device=dev),
-                 dt=torch.full((n,), h, dtype=torch.float64, device=dev))
+        st = _State.start(ctx, r0, v0, m, float(h))
         every = ctx.idx(torch.arange(n, dtype=torch.int32))
         acc = torch.empty((3, n), dtype=torch.float64, device=dev)
         ctx.predict(0.0)
-        ctx.force(every, 0.0, with_pot=False, acc=acc)
-        ctx.a.copy_(acc)
+        ctx.force(every, 0.0, with_pot=False, acc=st.a)
         checkpoints = []
         for s in range(steps):
             if s % era == 0:
-                checkpoints.append((s, ctx.r.clone(), ctx.v.clone(), ctx.a.clone()))
+                checkpoints.append((s, st.flat.clone()))
             _step(ctx, every, acc, s, h)
         fctx.tsbts = ctx
         fctx.meta = (h, steps, era)
@@ -104,24 +136,26 @@ class TsbtsLeapfrog(torch.autograd.Function):
         g = z()
         mbar = torch.zeros(n, dtype=torch.float64, device=dev)
         acc = torch.empty((3, n), dtype=torch.float64, device=dev)
-        ctx.bind(ctx.r, ctx.v, m, a=ctx.a, t_last=ctx.t_last, dt=ctx.dt)
-        for (s0, r_c, v_c, a_c) in reversed(fctx.checkpoints):
+        st = _State.like(ctx, fctx.checkpoints[0][1], m)
+        for (s0, flat) in reversed(fctx.checkpoints):
             s1 = min(s0 + era, steps)
-            # recompute the era from its checkpoint, keeping the positions of every step
-            ctx.r.copy_(r_c)
-            ctx.v.copy_(v_c)
-            ctx.a.copy_(a_c)
-            ctx.t_last.fill_(s0 * h)
+            # recompute the era from its checkpoint, keeping the positions of every step;
+            # the last step's are its prediction, its force is not needed
+            st.flat.copy_(flat)
             pos = []
-            for s in range(s0, s1):
+            for s in range(s0, s1 - 1):
                 _step(ctx, every, acc, s, h)
-                pos.append(ctx.r.clone())
+                pos.append(st.r.clone())
+            ctx.predict(s1 * h)
             for s in range(s1 - 1, s0 - 1, -1):
                 ctx.leapfrog_adjoint(0, h, rbar, vbar, abar, g)      # g = abar + h vbar / 2
-                ctx.load_positions(pos[s - s0], m, 0.0)
-                ctx.force_backward(every, 0.0, g, None, rbar, mbar)  # through a_{s+1}
+                tb = s1 * h
+                if s < s1 - 1:
+                    tb = 0.0
+                    ctx.load_positions(pos[s - s0], m, tb)
+                ctx.force_backward(every, tb, g, None, rbar, mbar)   # through a_{s+1}
                 ctx.leapfrog_adjoint(1, h, rbar, vbar, abar, g)      # adjoints of step s
-        ctx.load_positions(fctx.checkpoints[0][1], m, 0.0)
+        ctx.load_positions(_State(ctx, fctx.checkpoints[0][1]).r, m, 0.0)
         ctx.force_backward(every, 0.0, abar, None, rbar, mbar)      # through a_0
         return rbar, vbar, mbar, None, None, None, None
 
@@ -190,20 +224,15 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
         dev = ctx.device
         sched = BlockSchedule(ctx, dt, t_end)
         r0, v0, m = (x.detach().contiguous() for x in (r0, v0, m))
-        ctx.bind(r0.clone(), v0.clone(), m.clone(),
-                 t_last=torch.zeros(n, dtype=torch.float64, device=dev),
-                 dt=torch.tensor(sched.dt, dtype=torch.float64, device=dev))
-        every = ctx.idx(torch.arange(n, dtype=torch.int32))
+        st = _State.start(ctx, r0, v0, m, torch.tensor(sched.dt))
+        every = sched.sets[-1]
         buf = torch.empty(3 * n, dtype=torch.float64, device=dev)
-        acc = buf.view(3, n)
         ctx.predict(0.0)
-        ctx.force(every, 0.0, with_pot=False, acc=acc)
-        ctx.a.copy_(acc)
+        ctx.force(every, 0.0, with_pot=False, acc=st.a)
         checkpoints = []
         for s in range(sched.K):
             if s % era == 0:
-                checkpoints.append((s, ctx.r.clone(), ctx.v.clone(), ctx.a.clone(),
-                                    ctx.t_last.clone()))
+                checkpoints.append((s, st.flat.clone()))
             _block_step(ctx, sched, s, buf)
         fctx.tsbts = ctx
         fctx.sched = sched
@@ -227,22 +256,21 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
         mbar = torch.zeros(n, dtype=torch.float64, device=dev)
         buf = torch.empty(3 * n, dtype=torch.float64, device=dev)
         seeds = torch.empty(3 * n, dtype=torch.float64, device=dev)
-        first = fctx.checkpoints[0]
-        ctx.bind(first[1].clone(), first[2].clone(), m, a=first[3].clone(),
-                 t_last=first[4].clone(), dt=torch.tensor(sched.dt, dtype=torch.float64,
-                                                          device=dev))
-        state = (ctx.r, ctx.v, ctx.a, ctx.t_last)
-        for (s0, *ck) in reversed(fctx.checkpoints):
+        first = fctx.checkpoints[0][1]
+        st = _State.like(ctx, first, m)
+        for (s0, flat) in reversed(fctx.checkpoints):
             s1 = min(s0 + era, sched.K)
-            for dst, src in zip(state, ck):
-                dst.copy_(src)
-            pre = []
-            for s in range(s0, s1):
-                pre.append([x.clone() for x in state])
+            st.flat.copy_(flat)
+            # the states before the era's steps; the last one stays in place, and what its
+            # step gives is not needed
+            pre = [flat]
+            for s in range(s0, s1 - 1):
+                if s > s0:
+                    pre.append(st.flat.clone())
                 _block_step(ctx, sched, s, buf)
             for s in range(s1 - 1, s0 - 1, -1):
-                for dst, src in zip(state, pre[s - s0]):
-                    dst.copy_(src)
+                if s < s1 - 1:
+                    st.flat.copy_(pre[s - s0])
                 tb = sched.time(s)
                 idx = sched.active(s)
                 k = idx.numel()
@@ -251,22 +279,13 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
                 ctx.block_adjoint(0, idx, tb, rbar, vbar, abar, pbar, sd)
                 ctx.force_backward(idx, tb, sd, None, pbar, mbar)
                 ctx.block_adjoint(1, None, tb, rbar, vbar, abar, pbar, None)
-        ctx.load_positions(first[1], m, 0.0)
+        ctx.load_positions(_State(ctx, first).r, m, 0.0)
         ctx.force_backward(fctx.every, 0.0, abar, None, rbar, mbar)   # through a_0
         return rbar, vbar, mbar, None, None, None, None
 
 
 def tsbts_block_leapfrog(r0, v0, m, ctx: Context, dt, t_end: float, era: int = 16):
     return TsbtsBlockLeapfrog.apply(r0, v0, m, ctx, dt, t_end, era)
-
-
-def _state(ctx: Context):
-    return (ctx.r, ctx.v, ctx.a, ctx.t_last, ctx.dt)
-
-
-def _restore(ctx: Context, saved):
-    for dst, src in zip(_state(ctx), saved):
-        dst.copy_(src)
 
 
 def fixed_schedule(dt, t_end: float, era: float, passes: int):
@@ -334,18 +353,18 @@ class _DeviceSchedule:
             self.eras.append(passes)
 
 
-def _sched_pass(ctx: Context, steps, buf, use_history: bool, record: bool, pre=None,
-                dt_start=None):
+def _sched_pass(ctx: Context, st: _State, steps, buf, use_history: bool, record: bool,
+                pre=None, dt_start=None):
     """One pass over the listed block steps; record = keep its states as the next pass's
     interpolation source; pre = list receiving each step's pre-step state; dt_start =
     the steps of all particles when the pass starts (None: those of the state)."""
     if dt_start is not None:
-        ctx.dt.copy_(dt_start)
+        st.dt.copy_(dt_start)
     if record:
         ctx.history_begin()
     for (tb, idx, dtn) in steps:
         if pre is not None:
-            pre.append([x.clone() for x in _state(ctx)])
+            pre.append(st.flat.clone())
         k = idx.numel()
         acc = buf[:3 * k].view(3, k)
         ctx.predict(tb, use_history)
@@ -371,24 +390,20 @@ class TsbtsScheduleLeapfrog(torch.autograd.Function):
         n = ctx.n
         dev = ctx.device
         r0, v0, m = (x.detach().contiguous() for x in (r0, v0, m))
-        ctx.bind(r0.clone(), v0.clone(), m.clone(),
-                 t_last=torch.zeros(n, dtype=torch.float64, device=dev),
-                 dt=sched.dt0.clone())
+        st = _State.start(ctx, r0, v0, m, sched.dt0)
         every = ctx.idx(torch.arange(n, dtype=torch.int32))
         buf = torch.empty(3 * n, dtype=torch.float64, device=dev)
-        acc = buf.view(3, n)
         ctx.predict(0.0)
-        ctx.force(every, 0.0, with_pot=False, acc=acc)
-        ctx.a.copy_(acc)
+        ctx.force(every, 0.0, with_pot=False, acc=st.a)
         starts = []
         for passes in sched.eras:
-            start = [x.clone() for x in _state(ctx)]
+            start = st.flat.clone()
             starts.append(start)
             ctx.history_clear()
             for p, steps in enumerate(passes):
                 if p:
-                    _restore(ctx, start)
-                _sched_pass(ctx, steps, buf, p > 0, p < len(passes) - 1,
+                    st.flat.copy_(start)
+                _sched_pass(ctx, st, steps, buf, p > 0, p < len(passes) - 1,
                             dt_start=sched.pass_dt[len(starts) - 1][p])
         ctx.history_clear()
         fctx.tsbts = ctx
@@ -413,13 +428,12 @@ class TsbtsScheduleLeapfrog(torch.autograd.Function):
         buf = torch.empty(3 * n, dtype=torch.float64, device=dev)
         seeds = torch.empty(3 * n, dtype=torch.float64, device=dev)
         first = fctx.starts[0]
-        ctx.bind(first[0].clone(), first[1].clone(), m, a=first[2].clone(),
-                 t_last=first[3].clone(), dt=first[4].clone())
+        st = _State.like(ctx, first, m)
         for e in range(len(sched.eras) - 1, -1, -1):
             passes, start = sched.eras[e], fctx.starts[e]
             P = len(passes)
             # each particle's first record of a pass is its era-start state, at its own time
-            t_start = start[3].cpu().numpy()
+            t_start = _State(ctx, start).t_last.cpu().numpy()
             groups = [(float(t), ctx.idx(np.flatnonzero(t_start == t).astype(np.int32)))
                       for t in np.unique(t_start)]
             acc_r, acc_v, acc_a = z(), z(), z()
@@ -428,19 +442,19 @@ class TsbtsScheduleLeapfrog(torch.autograd.Function):
                 # interpolation source of pass p: pass p-1, rebuilt from the era start
                 ctx.history_clear()
                 for q in range(p):
-                    _restore(ctx, start)
-                    _sched_pass(ctx, passes[q], buf, q > 0, True,
+                    st.flat.copy_(start)
+                    _sched_pass(ctx, st, passes[q], buf, q > 0, True,
                                 dt_start=sched.pass_dt[e][q])
                 if p:
                     layout = ctx.history_layout()
                     hbar = torch.zeros((6, layout[0]), dtype=torch.float64, device=dev)
-                _restore(ctx, start)
+                st.flat.copy_(start)
                 pre = []
-                _sched_pass(ctx, passes[p], buf, p > 0, False, pre,
+                _sched_pass(ctx, st, passes[p], buf, p > 0, False, pre,
                             dt_start=sched.pass_dt[e][p])
                 rb, vb, ab = (rbar, vbar, abar) if p == P - 1 else (z(), z(), z())
                 for s in range(len(passes[p]) - 1, -1, -1):
-                    _restore(ctx, pre[s])
+                    st.flat.copy_(pre[s])
                     tb, idx, _ = passes[p][s]
                     k = idx.numel()
                     sd = seeds[:3 * k].view(3, k)
@@ -458,9 +472,9 @@ class TsbtsScheduleLeapfrog(torch.autograd.Function):
                 ctx.adjoint_accumulate(rb, vb, ab, acc_r, acc_v, acc_a)
                 later = (layout, hbar) if p else None
             rbar, vbar, abar = acc_r, acc_v, acc_a
-            _restore(ctx, start)
+            st.flat.copy_(start)
         ctx.history_clear()
-        ctx.load_positions(first[0], m, 0.0)
+        ctx.load_positions(_State(ctx, first).r, m, 0.0)
         ctx.force_backward(fctx.every, 0.0, abar, None, rbar, mbar)   # through a_0
         return rbar, vbar, mbar, None, None
 
