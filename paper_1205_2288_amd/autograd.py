@@ -79,11 +79,11 @@ class _State:
 
     @classmethod
     def start(cls, ctx: Context, r0, v0, m, dt):
-        """At rest in time at r0, v0 with steps dt, accelerations of the start positions."""
-        st = cls(ctx, torch.empty(11 * ctx.n, dtype=torch.float64, device=ctx.device))
+        """r0, v0 at time 0 with steps dt; zero accelerations, which the prediction at time 0
+        reads before the first force gives them."""
+        st = cls(ctx, torch.zeros(11 * ctx.n, dtype=torch.float64, device=ctx.device))
         st.r.copy_(r0.reshape(3, ctx.n))
         st.v.copy_(v0.reshape(3, ctx.n))
-        st.t_last.zero_()
         if isinstance(dt, float):
             st.dt.fill_(dt)
         else:

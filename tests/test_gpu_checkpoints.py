@@ -42,3 +42,14 @@ def test_checkpoint_spacing(kind, prec, n):
     assert all(np.isfinite(a).all() for a in ref)
     for era, view in ((1, False), (3, False), (STEPS + 5, False), (2, True)):
         assert all(np.array_equal(a, b) for a, b in zip(ref, _grads(kind, prec, n, era, view)))
+
+
+@pytest.mark.parametrize("kind", ["shared", "block"])
+def test_memory_left_by_others(kind):
+    # buffers that come from the allocator with another tensor's NaNs in them
+    ref = _grads(kind, "fp64", 300, 2, False)
+    for _ in range(3):
+        left = [torch.full((c * 300,), float("nan"), dtype=torch.float64, device="cuda")
+                for c in (1, 3, 3, 3, 6, 9, 10, 11, 11, 11, 12, 33)]
+        del left
+        assert all(np.array_equal(a, b) for a, b in zip(ref, _grads(kind, "fp64", 300, 2, False)))
