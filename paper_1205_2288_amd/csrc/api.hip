@@ -15,6 +15,7 @@
 
 namespace tsbts {
 int64_t backward_partials_needed(const tsbts_ctx *c, int n_act);
+int64_t backward_partials_reserve(const tsbts_ctx *c);
 }
 
 using namespace tsbts;
@@ -264,7 +265,7 @@ int tsbts_create(tsbts_ctx **out, int64_t n, double eps, int precision, int flag
   }
   if (!st) {
     const int64_t need = std::max({partial_elems_needed(c, static_cast<int>(n)),
-                                   backward_partials_needed(c, static_cast<int>(n)),
+                                   backward_partials_reserve(c),
                                    fused_partials_needed(c, static_cast<int>(n))});
     st = ensure_part(c, need);
   }

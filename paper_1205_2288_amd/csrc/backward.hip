@@ -154,16 +154,18 @@ __device__ __forceinline__ int wave_max_i(int x) {
 }
 
 // ---------------------------------------------------------------- source part
-template <class V, int NEWTON, int MASK>
+// UNR: columns in flight, by the number of waves to a SIMD (kShareBwdPairs).
+template <class V, int NEWTON, int MASK, int UNR>
 __device__ __forceinline__ void src_tile(const typename V::I &row, const Col<V> *sc, int cnt,
                                          int64_t k, typename V::F eps2, typename V::F acc[4]) {
+#pragma unroll UNR
   for (int cc = 0; cc < cnt; ++cc) {
     const Col<V> c = sc[cc];
     pair_src<V, NEWTON, MASK>(row, c, eps2, MASK && c.idx == k, acc);
   }
 }
 
-template <class V, int NEWTON>
+template <class V, int NEWTON, int UNR>
 __global__ __launch_bounds__(kWG) void k_bwd_src(BwdArgs A) {
   using F = typename V::F;
   __shared__ Col<V> sc[kTJ];
@@ -218,9 +220,9 @@ __global__ __launch_bounds__(kWG) void k_bwd_src(BwdArgs A) {
     }
     F acc[4] = {F(0), F(0), F(0), F(0)};
     if (__ballot(k >= tlo && k <= thi) != 0)
-      src_tile<V, NEWTON, 1>(row, sc, cnt, k, eps2, acc);
+      src_tile<V, NEWTON, 1, UNR>(row, sc, cnt, k, eps2, acc);
     else
-      src_tile<V, NEWTON, 0>(row, sc, cnt, k, eps2, acc);
+      src_tile<V, NEWTON, 0, UNR>(row, sc, cnt, k, eps2, acc);
 #pragma unroll
     for (int e = 0; e < 4; ++e) tot[e] += static_cast<double>(acc[e]);
   }
@@ -274,17 +276,56 @@ __global__ __launch_bounds__(kWG) void k_bwd_rows_reduce_wave(BwdArgs A) {
   A.gm[k] += tot[3];
 }
 
+// Many slices, or few rows: a workgroup per 64 consecutive rows whose kRowsWaves waves each
+// add a contiguous range of the slices, as the force's reduction does (N = 8192, 32
+// slices: 10.4 -> 4.8 us).  NV = 4: the source or both parts' rows, k_bwd_rows_reduce's
+// result; NV = 3: the target part's, k_bwd_tgt_reduce's.
+template <int NV, int SCALE_R>
+__global__ __launch_bounds__(64 * kRowsWaves) void k_bwd_reduce_rows(BwdArgs A, int n_rows) {
+  __shared__ double sums[kRowsWaves][NV][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int q = blockIdx.x * 64 + lane;
+  const int S = A.plan.n_slices;
+  const int L = (S + kRowsWaves - 1) / kRowsWaves;
+  const int s1 = min(S, (w + 1) * L);
+  double t[NV] = {};
+  if (q < n_rows) {
+    const int64_t stride = NV * static_cast<int64_t>(n_rows);
+#pragma unroll 4
+    for (int s = w * L; s < s1; ++s) {
+      const double *in = A.part + s * stride;
+#pragma unroll
+      for (int e = 0; e < NV; ++e) t[e] += in[e * static_cast<int64_t>(n_rows) + q];
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < NV; ++e) sums[w][e][lane] = t[e];
+  __syncthreads();
+  if (w >= NV || q >= n_rows) return;
+  // wave e adds value e of the ranges and its share of the result
+  double f = 0.0;
+#pragma unroll
+  for (int ww = 0; ww < kRowsWaves; ++ww) f += sums[ww][w][lane];
+  if (w == 3) {
+    A.gm[q] += f;
+  } else {
+    const int64_t k = NV == 4 ? q : A.idx[q];
+    const double mk = SCALE_R ? A.p64[P64_M * A.npad + k] : 1.0;
+    A.gr[w * A.n + k] += mk * f;
+  }
+}
+
 // ---------------------------------------------------------------- target part
-template <class V, int NEWTON, int MASK>
+template <class V, int NEWTON, int MASK, int UNR>
 __device__ __forceinline__ void tgt_tile(const typename V::I &row, const typename V::J *sj,
                                          const typename V::F gk[4], int64_t jbase, int64_t g,
                                          typename V::F eps2, typename V::F acc[3]) {
-#pragma unroll 2
+#pragma unroll UNR
   for (int jj = 0; jj < kTJ; ++jj)
     pair_tgt<V, NEWTON, MASK>(row, sj[jj], gk, eps2, MASK && (jbase + jj == g), acc);
 }
 
-template <class V, int NEWTON>
+template <class V, int NEWTON, int UNR>
 __global__ __launch_bounds__(kWG) void k_bwd_tgt(BwdArgs A) {
   using F = typename V::F;
   __shared__ typename V::J sj[kTJ];
@@ -312,9 +353,9 @@ __global__ __launch_bounds__(kWG) void k_bwd_tgt(BwdArgs A) {
     __syncthreads();
     F acc[3] = {F(0), F(0), F(0)};
     if (__ballot(g >= jbase && g < jbase + kTJ) != 0)
-      tgt_tile<V, NEWTON, 1>(row, sj, gk, jbase, g, eps2, acc);
+      tgt_tile<V, NEWTON, 1, UNR>(row, sj, gk, jbase, g, eps2, acc);
     else
-      tgt_tile<V, NEWTON, 0>(row, sj, gk, jbase, g, eps2, acc);
+      tgt_tile<V, NEWTON, 0, UNR>(row, sj, gk, jbase, g, eps2, acc);
 #pragma unroll
     for (int e = 0; e < 3; ++e) tot[e] += static_cast<double>(acc[e]);
   }
@@ -455,13 +496,13 @@ __global__ __launch_bounds__(kWG) void k_bwd_all(BwdArgs A) {
 // sums as k_bwd_all.  Used in float64 mode, where it measured ~4% faster than the LDS
 // form at N = 131072; in mixed precision it measured ~6% slower (eight scalar streams per
 // column against a single staged record), so the LDS form stays the default there.
-template <class V, int NEWTON, int MASK>
+template <class V, int NEWTON, int MASK, int CH>
 __device__ __forceinline__ void all_tile_scalar(const BwdArgs &A, const typename V::I &row,
                                                 const typename V::F gk[4], int64_t jbase,
                                                 int64_t k, typename V::F eps2,
                                                 typename V::F acc[7]) {
 #pragma unroll 4
-  for (int jj = 0; jj < kTJ; ++jj) {
+  for (int jj = 0; jj < CH; ++jj) {
     ColAll<V> c;
     c.p = V::load_j(A.p32, A.p64, A.npad, jbase + jj, 1.0f);
     c.g = load_g<V>(A, jbase + jj);
@@ -489,9 +530,9 @@ __global__ __launch_bounds__(kWG) void k_bwd_all_scalar(BwdArgs A) {
     const int64_t jbase = static_cast<int64_t>(jt) * kTJ;
     F acc[7] = {F(0), F(0), F(0), F(0), F(0), F(0), F(0)};
     if (__ballot(k >= jbase && k < jbase + kTJ) != 0)
-      all_tile_scalar<V, NEWTON, 1>(A, row, gk, jbase, k, eps2, acc);
+      all_tile_scalar<V, NEWTON, 1, kTJ>(A, row, gk, jbase, k, eps2, acc);
     else
-      all_tile_scalar<V, NEWTON, 0>(A, row, gk, jbase, k, eps2, acc);
+      all_tile_scalar<V, NEWTON, 0, kTJ>(A, row, gk, jbase, k, eps2, acc);
 #pragma unroll
     for (int e = 0; e < 7; ++e) tot[e] += static_cast<double>(acc[e]);
   }
@@ -509,6 +550,143 @@ __global__ __launch_bounds__(kWG) void k_bwd_all_scalar(BwdArgs A) {
   }
 }
 
+// ---------------------------------------------------------------- few rows, float64
+// The three sums for few particles or rows, where a tile of 256 columns for 256 rows at a
+// time leaves most of the chip idle: 64 rows to a workgroup whose kShare waves take CH
+// columns of a unit each, through scalar loads (of the active targets by their index), as
+// the force does for few targets (ShareShape).  The waves' sums are added in wave order.
+// Where it is used, and what it measured: kShareBwdPairs.
+template <int NV>
+__device__ __forceinline__ void share_rows_out(const BwdArgs &A, const double (&tot)[NV],
+                                               int64_t n_rows, int64_t q, int slice, int w,
+                                               int lane, int scale_r) {
+  __shared__ double red[kShare][NV][64];
+#pragma unroll
+  for (int e = 0; e < NV; ++e) red[w][e][lane] = tot[e];
+  __syncthreads();
+  if (w >= NV || q >= n_rows) return;
+  double f = 0.0;
+#pragma unroll
+  for (int u = 0; u < kShare; ++u) f += red[u][w][lane];
+  if (A.plan.n_slices > 1) {
+    A.part[(static_cast<int64_t>(slice) * NV + w) * n_rows + q] = f;
+  } else if (w == 3) {
+    A.gm[q] += f;
+  } else {
+    const int64_t k = NV == 4 ? q : A.idx[q];
+    A.gr[w * A.n + k] += scale_r ? A.p64[P64_M * A.npad + k] * f : f;
+  }
+}
+
+template <class V, int NEWTON, int CH>
+__global__ __launch_bounds__(kWG) void k_bwd_all_share(BwdArgs A) {
+  using F = typename V::F;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int rtile, slice;
+  split_tile(blockIdx.x, A.plan, rtile, slice);
+  if (slice >= A.plan.n_slices) return;
+  const int jt0 = slice * A.plan.tiles_per_slice;
+  const int jt1 = min(jt0 + A.plan.tiles_per_slice, A.n_ctiles);
+  const int64_t P = A.npad;
+  const int64_t k = static_cast<int64_t>(rtile) * 64 + lane;  // row particle (< npad)
+  const typename V::I row = V::load_i(A.p32, A.p64, P, k);
+  const F gk[4] = {static_cast<F>(A.gord[k]), static_cast<F>(A.gord[P + k]),
+                   static_cast<F>(A.gord[2 * P + k]), static_cast<F>(A.gord[3 * P + k])};
+  const double mk = A.p64[P64_M * P + k];
+  const F eps2 = in_vector(static_cast<F>(A.eps2));
+  double tot[7] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  for (int jt = jt0; jt < jt1; ++jt) {
+    const int64_t jbase = (static_cast<int64_t>(jt) * kShare + w) * CH;
+    if (jbase >= A.n) break;
+    F acc[7] = {F(0), F(0), F(0), F(0), F(0), F(0), F(0)};
+    if (__ballot(k >= jbase && k < jbase + CH) != 0)
+      all_tile_scalar<V, NEWTON, 1, CH>(A, row, gk, jbase, k, eps2, acc);
+    else
+      all_tile_scalar<V, NEWTON, 0, CH>(A, row, gk, jbase, k, eps2, acc);
+#pragma unroll
+    for (int e = 0; e < 7; ++e) tot[e] += static_cast<double>(acc[e]);
+  }
+  const double out4[4] = {mk * tot[0] + tot[4], mk * tot[1] + tot[5], mk * tot[2] + tot[6],
+                          tot[3]};
+  share_rows_out<4>(A, out4, A.n, k, slice, w, lane, 0);
+}
+
+template <class V, int NEWTON, int CH>
+__global__ __launch_bounds__(kWG) void k_bwd_src_share(BwdArgs A) {
+  using F = typename V::F;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int rtile, slice;
+  split_tile(blockIdx.x, A.plan, rtile, slice);
+  if (slice >= A.plan.n_slices) return;
+  const int ct0 = slice * A.plan.tiles_per_slice;
+  const int ct1 = min(ct0 + A.plan.tiles_per_slice, A.n_ctiles);
+  const int64_t P = A.npad;
+  const int64_t k = static_cast<int64_t>(rtile) * 64 + lane;  // row particle (< npad)
+  const typename V::I row = V::load_i(A.p32, A.p64, P, k);
+  const F eps2 = in_vector(static_cast<F>(A.eps2));
+  double tot[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int ct = ct0; ct < ct1; ++ct) {
+    const int q0 = (ct * kShare + w) * CH, q1 = min(q0 + CH, A.n_act);
+    F acc[4] = {F(0), F(0), F(0), F(0)};
+#pragma unroll 4
+    for (int q = q0; q < q1; ++q) {
+      Col<V> c;
+      c.idx = A.idx[q];
+      c.p = V::load_j(A.p32, A.p64, P, c.idx, 1.0f);
+      c.g.x = A.ga[q];
+      c.g.y = A.ga[A.n_act + q];
+      c.g.z = A.ga[2 * A.n_act + q];
+      c.g.w = A.gp ? A.gp[q] : 0.0;
+      pair_src<V, NEWTON, 1>(row, c, eps2, c.idx == k, acc);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) tot[e] += static_cast<double>(acc[e]);
+  }
+  share_rows_out<4>(A, tot, A.n, k, slice, w, lane, 1);
+}
+
+template <class V, int NEWTON, int MASK, int CH>
+__device__ __forceinline__ void tgt_tile_scalar(const BwdArgs &A, const typename V::I &row,
+                                                const typename V::F gk[4], int64_t jbase,
+                                                int64_t g, typename V::F eps2,
+                                                typename V::F acc[3]) {
+#pragma unroll 4
+  for (int jj = 0; jj < CH; ++jj)
+    pair_tgt<V, NEWTON, MASK>(row, V::load_j(A.p32, A.p64, A.npad, jbase + jj, 1.0f), gk, eps2,
+                              MASK && (jbase + jj == g), acc);
+}
+
+template <class V, int NEWTON, int CH>
+__global__ __launch_bounds__(kWG) void k_bwd_tgt_share(BwdArgs A) {
+  using F = typename V::F;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int itile, slice;
+  split_tile(blockIdx.x, A.plan, itile, slice);
+  if (slice >= A.plan.n_slices) return;
+  const int jt0 = slice * A.plan.tiles_per_slice;
+  const int jt1 = min(jt0 + A.plan.tiles_per_slice, A.n_ctiles);
+  const int q = itile * 64 + lane, qq = min(q, A.n_act - 1);
+  const int64_t g = A.idx[qq];
+  const typename V::I row = V::load_i(A.p32, A.p64, A.npad, g);
+  const F gk[4] = {static_cast<F>(A.ga[qq]), static_cast<F>(A.ga[A.n_act + qq]),
+                   static_cast<F>(A.ga[2 * A.n_act + qq]),
+                   static_cast<F>(A.gp ? A.gp[qq] : 0.0)};
+  const F eps2 = in_vector(static_cast<F>(A.eps2));
+  double tot[3] = {0.0, 0.0, 0.0};
+  for (int jt = jt0; jt < jt1; ++jt) {
+    const int64_t jbase = (static_cast<int64_t>(jt) * kShare + w) * CH;
+    if (jbase >= A.n) break;
+    F acc[3] = {F(0), F(0), F(0)};
+    if (__ballot(g >= jbase && g < jbase + CH) != 0)
+      tgt_tile_scalar<V, NEWTON, 1, CH>(A, row, gk, jbase, g, eps2, acc);
+    else
+      tgt_tile_scalar<V, NEWTON, 0, CH>(A, row, gk, jbase, g, eps2, acc);
+#pragma unroll
+    for (int e = 0; e < 3; ++e) tot[e] += static_cast<double>(acc[e]);
+  }
+  share_rows_out<3>(A, tot, A.n_act, q, slice, w, lane, 0);
+}
+
 SplitPlan plan_src(const BwdArgs &A) {
   return plan_split(A.npad, 1, (A.n_act + kTJ - 1) / kTJ, A.blocks);
 }
@@ -517,9 +695,34 @@ SplitPlan plan_tgt(const BwdArgs &A) {
 }
 SplitPlan plan_all(const BwdArgs &A) { return plan_split(A.npad, 1, A.npad / kTJ, A.blocks); }
 
+// Float64 calls in the shared-row form (the automatic kernel form only): up to
+// kShareBwdPairs pairs of a target and a particle.  Measured (us, tiles of 256, this form):
+// 40 of N = 256 30.6, 11.3; 750 of 3000 53.9, 20.9; all of 3000 40.2, 27.3; 1024 of 16384
+// 60.8, 54.6; 4096 of 8192 87.5, 89.0; 7502 of 30011 477, 506.  In mixed precision, with
+// units of 256 columns (other units would be other float32 sums), the scalar operands cost
+// more than they save: 750 of 3000 51.6, 63.8.  There the LDS kernels of a partial set take
+// four columns at a time below the same limit, two above it (two, four): 1500 of 3000 52.4,
+// 46.0; 1024 of 16384 57.5, 50.7; 4096 of 16384 107, 107; 8192 of 131072 1200, 1225.
+constexpr int64_t kShareBwdPairs = int64_t(1) << 25;
+bool share_bwd(const tsbts_ctx *c, int64_t n_act) {
+  return c->precision == TSBTS_FP64 && force_scalar_j(c) && c->tune_chunk == 0 &&
+         c->n * n_act < kShareBwdPairs;
+}
+
+// Rows up to which k_bwd_reduce_rows also serves few slices (a thread per row is too few).
+constexpr int64_t kFewRows = 16384;
+bool reduce_by_rows(int n_slices, int64_t n_rows) {
+  return n_slices > 1 && ((n_slices <= kRowsFewSlices && n_rows <= kFewRows) ||
+                          use_rows_reduce(n_slices, n_rows));
+}
+
 template <int SCALE_R>
 void reduce_rows(BwdArgs &A, hipStream_t st) {
-  if (use_wave_reduce(A.plan.n_slices, A.n)) {
+  if (reduce_by_rows(A.plan.n_slices, A.n)) {
+    const int nb = static_cast<int>((A.n + 63) / 64);
+    hipLaunchKernelGGL((k_bwd_reduce_rows<4, SCALE_R>), dim3(nb), dim3(64 * kRowsWaves), 0, st,
+                       A, static_cast<int>(A.n));
+  } else if (use_wave_reduce(A.plan.n_slices, A.n)) {
     const int nb = static_cast<int>((A.n + kWG / 64 - 1) / (kWG / 64));
     hipLaunchKernelGGL(k_bwd_rows_reduce_wave<SCALE_R>, dim3(nb), dim3(kWG), 0, st, A);
   } else if (A.plan.n_slices > 1) {
@@ -528,8 +731,35 @@ void reduce_rows(BwdArgs &A, hipStream_t st) {
   }
 }
 
+void reduce_targets(BwdArgs &A, hipStream_t st) {
+  if (reduce_by_rows(A.plan.n_slices, A.n_act)) {
+    const int nb = (A.n_act + 63) / 64;
+    hipLaunchKernelGGL((k_bwd_reduce_rows<3, 0>), dim3(nb), dim3(64 * kRowsWaves), 0, st, A,
+                       A.n_act);
+  } else if (use_wave_reduce(A.plan.n_slices, A.n_act)) {
+    const int nb = (A.n_act + kWG / 64 - 1) / (kWG / 64);
+    hipLaunchKernelGGL(k_bwd_tgt_reduce_wave, dim3(nb), dim3(kWG), 0, st, A);
+  } else if (A.plan.n_slices > 1) {
+    const int nb = (A.n_act + kWG - 1) / kWG;
+    hipLaunchKernelGGL(k_bwd_tgt_reduce, dim3(nb), dim3(kWG), 0, st, A);
+  }
+}
+
+// Run a shared-row kernel in its shape, `tiny` or `small` columns to a wave and unit.
+using BwdKernel = void (*)(BwdArgs);
+void launch_share(BwdArgs &A, const ShareShape &s, BwdKernel tiny, BwdKernel small,
+                  hipStream_t st) {
+  A.plan = s.plan;
+  A.n_ctiles = s.n_units;
+  hipLaunchKernelGGL(s.chunk == kChunkTiny ? tiny : small, dim3(A.plan.nblk), dim3(kWG), 0, st,
+                     A);
+}
+
 template <class V, int NEWTON>
 hipError_t run(BwdArgs &A, hipStream_t st, tsbts_ctx *c) {
+  constexpr bool kF64 = sizeof(typename V::F) == 8;
+  const bool share = kF64 && share_bwd(c, A.n_act);
+  const bool few = A.n * A.n_act < kShareBwdPairs;
   if (A.n_act == A.n) {
     // every particle is active (the active set is a permutation of all particles)
     const int64_t cnt = A.n_act + (A.npad - A.n);
@@ -540,32 +770,52 @@ hipError_t run(BwdArgs &A, hipStream_t st, tsbts_ctx *c) {
       if (sym_plan(c, 4, 8, c->precision == TSBTS_FP64 ? 8 : 4, &plan))
         return launch_bwd_sym(c, plan, A.gp != nullptr, A.gr, A.gm, st);
     }
-    A.plan = plan_all(A);
-    A.n_ctiles = static_cast<int>(A.npad / kTJ);
-    if (A.scalar_j)
-      hipLaunchKernelGGL((k_bwd_all_scalar<V, NEWTON>), dim3(A.plan.nblk), dim3(kWG), 0, st,
-                         A);
-    else
-      hipLaunchKernelGGL((k_bwd_all<V, NEWTON>), dim3(A.plan.nblk), dim3(kWG), 0, st, A);
+    if (share) {
+      if constexpr (kF64)
+        launch_share(A, share_split(A.n, A.n, 0), k_bwd_all_share<V, NEWTON, kChunkTiny>,
+                     k_bwd_all_share<V, NEWTON, kChunkSmall>, st);
+    } else {
+      A.plan = plan_all(A);
+      A.n_ctiles = static_cast<int>(A.npad / kTJ);
+      if (A.scalar_j)
+        hipLaunchKernelGGL((k_bwd_all_scalar<V, NEWTON>), dim3(A.plan.nblk), dim3(kWG), 0, st,
+                           A);
+      else
+        hipLaunchKernelGGL((k_bwd_all<V, NEWTON>), dim3(A.plan.nblk), dim3(kWG), 0, st, A);
+    }
     reduce_rows<0>(A, st);
     return hipGetLastError();
   }
   // source part over all particles
-  A.plan = plan_src(A);
-  A.n_ctiles = (A.n_act + kTJ - 1) / kTJ;
-  hipLaunchKernelGGL((k_bwd_src<V, NEWTON>), dim3(A.plan.nblk), dim3(kWG), 0, st, A);
+  if (share) {
+    if constexpr (kF64)
+      launch_share(A, share_split(A.n, A.n_act, 0), k_bwd_src_share<V, NEWTON, kChunkTiny>,
+                   k_bwd_src_share<V, NEWTON, kChunkSmall>, st);
+  } else {
+    A.plan = plan_src(A);
+    A.n_ctiles = (A.n_act + kTJ - 1) / kTJ;
+    if (few)
+      hipLaunchKernelGGL((k_bwd_src<V, NEWTON, kF64 ? 2 : 4>), dim3(A.plan.nblk), dim3(kWG), 0,
+                         st, A);
+    else
+      hipLaunchKernelGGL((k_bwd_src<V, NEWTON, 2>), dim3(A.plan.nblk), dim3(kWG), 0, st, A);
+  }
   reduce_rows<1>(A, st);
   // target part over the active set
-  A.plan = plan_tgt(A);
-  A.n_ctiles = static_cast<int>(A.npad / kTJ);
-  hipLaunchKernelGGL((k_bwd_tgt<V, NEWTON>), dim3(A.plan.nblk), dim3(kWG), 0, st, A);
-  if (use_wave_reduce(A.plan.n_slices, A.n_act)) {
-    const int nb = (A.n_act + kWG / 64 - 1) / (kWG / 64);
-    hipLaunchKernelGGL(k_bwd_tgt_reduce_wave, dim3(nb), dim3(kWG), 0, st, A);
-  } else if (A.plan.n_slices > 1) {
-    const int nb = (A.n_act + kWG - 1) / kWG;
-    hipLaunchKernelGGL(k_bwd_tgt_reduce, dim3(nb), dim3(kWG), 0, st, A);
+  if (share) {
+    if constexpr (kF64)
+      launch_share(A, share_split(A.n_act, A.n, 0), k_bwd_tgt_share<V, NEWTON, kChunkTiny>,
+                   k_bwd_tgt_share<V, NEWTON, kChunkSmall>, st);
+  } else {
+    A.plan = plan_tgt(A);
+    A.n_ctiles = static_cast<int>(A.npad / kTJ);
+    if (few)
+      hipLaunchKernelGGL((k_bwd_tgt<V, NEWTON, kF64 ? 2 : 4>), dim3(A.plan.nblk), dim3(kWG), 0,
+                         st, A);
+    else
+      hipLaunchKernelGGL((k_bwd_tgt<V, NEWTON, 2>), dim3(A.plan.nblk), dim3(kWG), 0, st, A);
   }
+  reduce_targets(A, st);
   return hipGetLastError();
 }
 
@@ -577,17 +827,25 @@ int64_t backward_partials_needed(const tsbts_ctx *c, int n_act) {
   A.npad = c->npad;
   A.n_act = n_act;
   A.blocks = c->tune_blocks;
-  int64_t need = 0;
-  if (n_act == c->n) {
-    const SplitPlan a = plan_all(A);
-    if (a.n_slices > 1) need = static_cast<int64_t>(a.n_slices) * 4 * c->n;
-    return need;
-  }
-  const SplitPlan s = plan_src(A);
-  const SplitPlan t = plan_tgt(A);
-  if (s.n_slices > 1) need = static_cast<int64_t>(s.n_slices) * 4 * c->n;
-  if (t.n_slices > 1) need = std::max<int64_t>(need, static_cast<int64_t>(t.n_slices) * 3 * n_act);
-  return need;
+  const auto slices = [&](int64_t n, int nv) {
+    return n > 1 ? n * nv * (nv == 4 ? c->n : n_act) : int64_t(0);
+  };
+  const bool share = share_bwd(c, n_act);
+  if (n_act == c->n)
+    return slices((share ? share_split(c->n, c->n, 0).plan : plan_all(A)).n_slices, 4);
+  return std::max(
+      slices((share ? share_split(c->n, n_act, 0).plan : plan_src(A)).n_slices, 4),
+      slices((share ? share_split(n_act, c->n, 0).plan : plan_tgt(A)).n_slices, 3));
+}
+
+// What a context reserves, so that no later adjoint call has to allocate: the all-active
+// call's partials and bounds of the shared-row forms' over every active set.
+int64_t backward_partials_reserve(const tsbts_ctx *c) {
+  const int64_t n = c->n, most = (n + kShare * kChunkTiny - 1) / (kShare * kChunkTiny);
+  const int64_t tiles = (n + 63) / 64, want = (2048 + tiles - 1) / tiles;
+  const int64_t need = backward_partials_needed(c, static_cast<int>(n));
+  if (c->precision != TSBTS_FP64) return need;
+  return std::max({need, 4 * n * std::min(want, most), 3 * (2048 * 64 + n)});
 }
 
 hipError_t launch_backward(tsbts_ctx *c, const int32_t *idx, int n_act, const double *ga,

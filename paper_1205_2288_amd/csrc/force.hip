@@ -834,15 +834,14 @@ SplitPlan plan_split(int64_t n_targets, int ipl, int64_t n_jtiles, int target_bl
   return p;
 }
 
-namespace {
-
-ShareShape share_shape(const tsbts_ctx *c, int n_act, int chunk) {
+ShareShape share_split(int64_t n_targets, int64_t n_cols, int chunk) {
   ShareShape s;
-  const int64_t itiles = (n_act + 63) / 64;
+  const int64_t itiles = (n_targets + 63) / 64;
   if (!chunk)
-    chunk = itiles * (c->npad / (kShare * kChunkSmall)) < 512 ? kChunkTiny : kChunkSmall;
+    chunk = itiles * (round_up(n_cols, kPad) / (kShare * kChunkSmall)) < 512 ? kChunkTiny
+                                                                             : kChunkSmall;
   s.chunk = chunk;
-  s.n_units = static_cast<int>((c->n + kShare * chunk - 1) / (kShare * chunk));
+  s.n_units = static_cast<int>((n_cols + kShare * chunk - 1) / (kShare * chunk));
   // about 2048 workgroups, and few slices for the rows reduction: at most half of what it
   // takes unless each would hold several units
   const int64_t cap = s.n_units >= 2 * kRowsFewSlices ? kRowsFewSlices : kRowsFewSlices / 2;
@@ -855,6 +854,8 @@ ShareShape share_shape(const tsbts_ctx *c, int n_act, int chunk) {
   return s;
 }
 
+namespace {
+
 bool share_applies(const tsbts_ctx *c, int n_act) {
   return force_scalar_j(c) && c->tune_chunk == 0 && n_act < kShareMaxAct;
 }
@@ -863,7 +864,7 @@ bool share_applies(const tsbts_ctx *c, int n_act) {
 
 ShareShape share_force(const tsbts_ctx *c, int n_act) {
   if (!share_applies(c, n_act)) return ShareShape{};
-  return share_shape(c, n_act, c->precision == TSBTS_FP64 ? 0 : scalar_chunk(c, n_act, 1));
+  return share_split(n_act, c->n, c->precision == TSBTS_FP64 ? 0 : scalar_chunk(c, n_act, 1));
 }
 
 ShareShape share_step(const tsbts_ctx *c, int n_act) {
@@ -871,7 +872,7 @@ ShareShape share_step(const tsbts_ctx *c, int n_act) {
   // issue faster than scalar ones (512 targets at N = 131072 54 against 62 us)
   const bool staged = c->precision == TSBTS_MIXED && c->npad >= 65536 && n_act > 256;
   if (!share_applies(c, n_act) || staged) return ShareShape{};
-  return share_shape(c, n_act, 0);
+  return share_split(n_act, c->n, 0);
 }
 
 int64_t force_partial_elems(const tsbts_ctx *c, int n_act, int blocks) {

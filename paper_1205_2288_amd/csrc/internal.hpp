@@ -453,6 +453,8 @@ struct ShareShape {
 inline uint32_t *share_done(const tsbts_ctx *c, int which) {
   return c->done + 2 + which * kShareTiles;
 }
+// The split of n_cols j-particles for n_targets (chunk 0: 64, or 16 for few).
+ShareShape share_split(int64_t n_targets, int64_t n_cols, int chunk);
 ShareShape share_force(const tsbts_ctx *c, int n_act);
 ShareShape share_step(const tsbts_ctx *c, int n_act);
 // The criterion kernel likewise for large active sets (from 8192 targets, two targets per
