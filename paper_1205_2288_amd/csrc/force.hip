@@ -29,15 +29,11 @@
 namespace tsbts {
 namespace {
 
-// The time-step criterion of the targets after their correction, taken by the last
-// workgroup of a small predicted launch (small_criterion_last).
+// The time-step criterion of the targets after their correction, taken by a small
+// predicted launch of one workgroup (small_criterion).
 struct CritArgs {
   int on;
   int64_t n;  // particles; j >= n are padding
-  const float *p32;
-  const double *p64;
-  const double *v64;
-  int64_t npad;
   double eps2;
   double eta;
   double *dtc;
@@ -380,18 +376,16 @@ __device__ __forceinline__ void small_reduce_last(const ForceArgs &A, const int 
   }
 }
 
-// The criterion of the targets after their correction, by the launch's last workgroup
-// alone (a small active set on few particles): lane l takes the particles l, l + 256, ...
-// against kCritGroup targets at a time, the records of kCritBatch tiles loaded before
-// their pairs so that one memory latency serves several tiles; the maxima and negated
-// minima are then combined over the wave (wave_reduce_many) and over the 4 waves.  Max
-// and min are exact, so dtc is what the criterion kernels give bit for bit.  The targets'
-// corrected velocities were stored by this workgroup; every other particle's predicted
-// record was stored before its workgroup counted itself in, so last_workgroup made it
-// visible.  ONE: this workgroup is the only one, each thread's particle is `own` (as
-// predicted) and the targets' positions and corrected velocities are si and tv in LDS.
+// The criterion of the targets after their correction, by a launch of one workgroup (at
+// most kTJ particles): each thread takes its particle `own` (as predicted; a target's with
+// its new velocity) against kCritGroup targets at a time, whose positions and corrected
+// velocities are si and tv in LDS; the maxima and negated minima are then combined over
+// the wave (wave_reduce_many) and over the 4 waves.  Max and min are exact, so dtc is what
+// the criterion kernels give bit for bit.  With more workgroups a second launch is faster:
+// the last workgroup alone would walk all particles behind a write-back of the caches (a
+// block step of 5 targets of 2000, mixed, 28.0 against 21.6 us, of 6 of 300 21.3 against
+// 19.7).
 constexpr int kCritGroup = 8;
-constexpr int kCritBatch = 4;
 
 template <class J>
 __device__ __forceinline__ void set_velocity(J &r, const double *v) {
@@ -406,59 +400,37 @@ __device__ __forceinline__ void set_velocity(J &r, const double *v) {
   }
 }
 
-template <class V, bool ONE>
-__device__ __forceinline__ void small_criterion_last(const ForceArgs &A, const int *sg,
-                                                     const typename V::I *si,
-                                                     const double (*tv)[3],
-                                                     typename StepRec<V>::J own) {
+template <class V>
+__device__ __forceinline__ void small_criterion(const ForceArgs &A, const int *sg,
+                                                const typename V::I *si, const double (*tv)[3],
+                                                typename StepRec<V>::J own) {
   using F = typename V::F;
   using SR = StepRec<V>;
   constexpr int G = kCritGroup;
-  constexpr int kBatch = ONE ? 1 : kCritBatch;
   __shared__ typename SR::I ti[kSmallAct];
   __shared__ F red[kSmallAct][2][kWG / 64];
   const CritArgs &C = A.crit;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   __syncthreads();
-  if constexpr (ONE) {
-    if (tid < A.n_act) {
-      ti[tid].p = si[tid];
-      ti[tid].vx = static_cast<decltype(ti[tid].vx)>(tv[tid][0]);
-      ti[tid].vy = static_cast<decltype(ti[tid].vy)>(tv[tid][1]);
-      ti[tid].vz = static_cast<decltype(ti[tid].vz)>(tv[tid][2]);
-    }
-    for (int q = 0; q < A.n_act; ++q)
-      if (sg[q] == tid) set_velocity(own, tv[q]);
-  } else if (tid < A.n_act) {
-    ti[tid] = load_iv<V>(C, sg[tid]);
+  if (tid < A.n_act) {
+    ti[tid].p = si[tid];
+    ti[tid].vx = static_cast<decltype(ti[tid].vx)>(tv[tid][0]);
+    ti[tid].vy = static_cast<decltype(ti[tid].vy)>(tv[tid][1]);
+    ti[tid].vz = static_cast<decltype(ti[tid].vz)>(tv[tid][2]);
   }
+  for (int q = 0; q < A.n_act; ++q)
+    if (sg[q] == tid) set_velocity(own, tv[q]);
   __syncthreads();
   const F eps2 = static_cast<F>(C.eps2);
-  const int n_tiles = ONE ? 1 : static_cast<int>((C.n + kTJ - 1) / kTJ);
   const F inf = sizeof(F) == 4 ? static_cast<F>(__builtin_inff()) : static_cast<F>(__builtin_inf());
   for (int q0 = 0; q0 < A.n_act; q0 += G) {
     F qm[G], sm[G];
 #pragma unroll
     for (int u = 0; u < G; ++u) {
+      const int q = q0 + u;
       qm[u] = F(0);
       sm[u] = inf;
-    }
-    for (int jt = 0; jt < n_tiles; jt += kBatch) {
-      typename SR::J J[kBatch];
-#pragma unroll
-      for (int b = 0; b < kBatch; ++b)
-        if (jt + b < n_tiles)
-          J[b] = ONE ? own : load_jv<V>(C, static_cast<int64_t>(jt + b) * kTJ + tid);
-#pragma unroll
-      for (int b = 0; b < kBatch; ++b) {
-        if (jt + b >= n_tiles) break;
-        const int64_t j = static_cast<int64_t>(jt + b) * kTJ + tid;
-#pragma unroll
-        for (int u = 0; u < G; ++u) {
-          const int q = q0 + u;
-          if (q < A.n_act) pair_step(ti[q], J[b], eps2, j == sg[q] || j >= C.n, qm[u], sm[u]);
-        }
-      }
+      if (q < A.n_act) pair_step(ti[q], own, eps2, tid == sg[q] || tid >= C.n, qm[u], sm[u]);
     }
     F x[2 * G];
 #pragma unroll
@@ -637,15 +609,11 @@ __global__ __launch_bounds__(kWG) void k_force_small_pred(ForceArgs A, PredictAr
     if (tid < A.n_act)
       finish<V, NEWTON>(A, tid, sg[tid], one[tid], one[A.n_act + tid], one[2 * A.n_act + tid],
                         one[3 * A.n_act + tid], &ts, tv[tid]);
-    if (A.crit.on) small_criterion_last<V, true>(A, sg, si, tv, Jc);
+    if (A.crit.on) small_criterion<V>(A, sg, si, tv, Jc);
     return;
   }
-  // (the criterion also reads the planes the other workgroups stored)
-  if (!A.fuse_reduce ||
-      !(A.crit.on ? last_workgroup(A.done) : last_workgroup_partials(A.done, gridDim.x)))
-    return;
-  small_reduce_last<V, NEWTON>(A, sg, &ts);
-  if (A.crit.on) small_criterion_last<V, false>(A, sg, si, tv, Jc);
+  if (A.fuse_reduce && last_workgroup_partials(A.done, gridDim.x))
+    small_reduce_last<V, NEWTON>(A, sg, &ts);
 }
 
 // Add the slices' partials in slice order and finish (scale, sign).
@@ -970,10 +938,7 @@ int small_act_limit(const tsbts_ctx *c) {
 }
 
 bool small_criterion_fused(const tsbts_ctx *c, int n_act) {
-  const int64_t tiles = used_tiles(c);
-  const int groups = (n_act + kCritGroup - 1) / kCritGroup;
-  return n_act <= small_act_limit(c) && fuse_small_reduce(static_cast<int>(tiles), 4 * n_act) &&
-         tiles * groups <= kCritFuseTiles;
+  return n_act <= small_act_limit(c) && used_tiles(c) == 1;
 }
 
 hipError_t launch_force_predicted(tsbts_ctx *c, const int32_t *idx, int n_act, double t_block,
@@ -985,10 +950,6 @@ hipError_t launch_force_predicted(tsbts_ctx *c, const int32_t *idx, int n_act, d
   if (dtc && corr && small_criterion_fused(c, n_act)) {
     A.crit.on = 1;
     A.crit.n = c->n;
-    A.crit.p32 = c->p32;
-    A.crit.p64 = c->p64;
-    A.crit.v64 = c->v64;
-    A.crit.npad = c->npad;
     A.crit.eps2 = c->eps * c->eps;
     A.crit.eta = eta;
     A.crit.dtc = dtc;

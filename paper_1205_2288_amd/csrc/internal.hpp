@@ -78,7 +78,7 @@ struct tsbts_ctx {
                                                       // (mapped pinned memory)
   int32_t *idx_seen = nullptr;  // [n] occurrence counters of the check
   // finished-workgroup counts of the launches whose last workgroup reduces the partials
-  // (last_workgroup), zero between launches: the small-set force [0] and criterion [1],
+  // (last_workgroup_partials), zero between launches: the small-set force [0] and criterion [1],
   // then kShareTiles each for the tiles of 64 targets of the two (share_done)
   uint32_t *done = nullptr;
   // symmetric all-targets kernels: work items (int4) and partials
@@ -277,35 +277,17 @@ __device__ __forceinline__ T wave_reduce_many(T (&x)[NV], int lane, Op op) {
   return x[0];
 }
 
-// Whether this workgroup is the last of its launch (a one-dimensional grid) to get here,
-// for a launch whose last workgroup finishes a reduction over every workgroup's stores.
-// Every thread makes its stores visible device-wide (agent-scope fence: across the XCDs'
-// separate L2 caches) before one thread counts the workgroup in `done`; the last one
-// resets the count to zero for the next launch and, after an acquire fence of every
-// thread, sees all stores made before the other workgroups counted.  No workgroup waits
-// for another.  Every thread of the workgroup must call it.
-__device__ __forceinline__ bool last_workgroup(uint32_t *done) {
-  __shared__ uint32_t last;
-  __threadfence();
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const uint32_t before = atomicAdd(done, 1u);
-    last = before + 1 == gridDim.x ? 1u : 0u;
-    if (last) atomicExch(done, 0u);
-  }
-  __syncthreads();
-  if (!last) return false;
-  __threadfence();
-  return true;
-}
-
-// The same where everything the last workgroup reads of the others' was written by
-// store_partial and is read by load_partial, of the `count` workgroups of `done`: those pass the caches that the XCDs do not
-// share (relaxed atomics of agent scope), so no cache is written back or emptied; every
-// thread waits until its stores have arrived before the workgroup is counted.  With the
+// Whether this workgroup is the last of `count` to get here, for a launch whose last
+// workgroup finishes a reduction over the others' partials.  Everything it reads of theirs
+// was written by store_partial and is read by load_partial: those pass the caches that the
+// XCDs do not share (relaxed atomics of agent scope), so no cache is written back or
+// emptied; every thread waits until its stores have arrived before one thread counts the
+// workgroup in `done`.  The last one resets the count to zero for the next launch.  No
+// workgroup waits for another.  Every thread of the workgroup must call it.  With the
 // register moves above instead of LDS shuffles, small calls on N = 4096 took (us, force /
-// criterion): 4 targets 7.0 / 8.0 -> 5.1 / 5.7, 16 targets 9.7 / 8.9 -> 7.3 / 6.9; one
-// target, whose 64 mostly empty parts are no longer added, 8.7 / 10.3 -> 4.7 / 5.3.
+// criterion, before with agent-scope fences): 4 targets 7.0 / 8.0 -> 5.1 / 5.7, 16 targets
+// 9.7 / 8.9 -> 7.3 / 6.9; one target, whose 64 mostly empty parts are no longer added,
+// 8.7 / 10.3 -> 4.7 / 5.3.
 __device__ __forceinline__ void store_partial(double *p, double x) {
   __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -604,10 +586,8 @@ hipError_t launch_force_predicted(tsbts_ctx *c, const int32_t *idx, int n_act, d
                                   const CorrectArgs *corr, const PendingSteps *pend = nullptr,
                                   const InlineIdx *in = nullptr, double eta = 0.0,
                                   double *dtc = nullptr);
-// Whether launch_force_predicted takes the criterion of n_act targets itself: the one
-// workgroup's passes over the particles are short (j-tiles times groups of 8 targets at
-// most kCritFuseTiles).
-constexpr int kCritFuseTiles = 8;
+// Whether launch_force_predicted takes the criterion of n_act targets itself: launches of
+// one workgroup.
 bool small_criterion_fused(const tsbts_ctx *c, int n_act);
 // Symmetric all-targets criterion (timestep_sym.hip); plan from sym_plan.  With `set`, the
 // kernels run on that particle set instead of the context's predicted arrays; with `raw`,
