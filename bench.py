@@ -73,13 +73,13 @@ TRAFFIC_KIB = {
     "k_force_sym": (134838.2, 363358.0,
         ("force_sym.hip", "sym.hpp", "force_pair.hpp", "pair.hpp", "internal.hpp",
          "correct.hpp"),
-        "eae373964a4c41fd"),
+        "22d539811e6e2289"),
     "k_bwd_sym": (210271.6, 396288.0,
         ("backward_sym.hip", "sym.hpp", "pair.hpp", "internal.hpp"),
-        "574bbe3b71ad5b77"),
+        "1d5043e8a01cc2c9"),
     "k_energy_pairs": (33877.6, 256.0,
         ("energy.hip", "internal.hpp"),
-        "784d19e45ba1a893"),
+        "6a52d9e8fe1fa423"),
 }
 
 

@@ -80,12 +80,14 @@ int tsbts_destroy(tsbts_ctx *ctx);
 /* Launch-shape tuning of the pair kernels (force, criterion, adjoint); host-side only.
  *   TSBTS_TUNE_BLOCKS: workgroups a split-j launch aims for (64 .. 65536; default 8192)
  *   TSBTS_TUNE_IPL:    kernel form of the force and criterion (0 = automatic: the force,
- *                      and the criterion from 8192 targets, read the j-particles through
- *                      wave-uniform scalar loads; 1, 2 or 4 = the LDS-staged kernels with
- *                      that many target particles per lane)
+ *                      and the criterion of few targets or many, read the j-particles
+ *                      through wave-uniform scalar loads, sets below 4096 targets with
+ *                      the waves of a workgroup sharing 64 targets; 1, 2 or 4 = the
+ *                      LDS-staged kernels with that many target particles per lane)
  *   TSBTS_TUNE_CHUNK:  j-particles per split unit of the scalar-load kernels (0 =
  *                      automatic: 64 when 256-particle units would give fewer than 512
- *                      workgroups, else 256; or 64, 256)
+ *                      workgroups, else 256, and 16 in the float64 force and adjoint and
+ *                      the criterion of few targets; or 64, 256)
  *   TSBTS_TUNE_SYMMETRIC: when every particle is a target (n_active = n), evaluate each
  *                      unordered pair once for both of its particles (0 = never, 1 =
  *                      always, 2 = automatic: from 32768 particles while the partial
@@ -115,6 +117,11 @@ int tsbts_destroy(tsbts_ctx *ctx);
  *                      a repeated index leaves undefined output rows when every particle
  *                      is a target and the symmetric kernels serve the call, or when a
  *                      split call does).
+ * With all of these automatic, a criterion call of k targets with n (k - 1300) >= 9.4e7
+ * (n (2 k - 1300) in float64) runs over a spatial order of the particles that leaves out
+ * pairs which cannot change a target's extremes (the same values bit for bit).  The first
+ * such call on a context allocates a few hundred bytes per particle; where that fails, or
+ * while its stream is captured, the other kernels serve it.
  * Results do not depend on these except through the order of float64 tile sums.
  * Invalid values return TSBTS_EINVAL and leave the setting unchanged. */
 int tsbts_tune(tsbts_ctx *ctx, int param, int value);

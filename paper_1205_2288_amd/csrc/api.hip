@@ -265,7 +265,7 @@ int tsbts_create(tsbts_ctx **out, int64_t n, double eps, int precision, int flag
   }
   if (!st) {
     const int64_t need = std::max({partial_elems_needed(c, static_cast<int>(n)),
-                                   backward_partials_reserve(c),
+                                   backward_partials_reserve(c), share_partials_reserve(c),
                                    fused_partials_needed(c, static_cast<int>(n))});
     st = ensure_part(c, need);
   }
@@ -533,7 +533,7 @@ int tsbts_timestep(tsbts_ctx *c, const int32_t *idx, int32_t n_act, double eta, 
   if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, TSBTS_EINVAL, "eta must be > 0");
   if (!c->have_pred) return fail(c, TSBTS_ESTATE, "no predicted particle arrays");
   // without the buffers of the spatial order the other kernels serve the call
-  if (!cells_criterion_applies(c, n_act) || !cells_prepare(c)) {
+  if (!cells_criterion_applies(c, n_act) || !cells_prepare(c, stream)) {
     if (int s = ensure_part(c, partial_elems_needed(c, n_act))) return s;
     if (criterion_sym_applies(c, n_act)) {
       const int vb = c->precision == TSBTS_FP64 ? 8 : 4;

@@ -49,7 +49,7 @@ hipError_t launch_cell_sort(const CellSort &s, const double *p64, const double *
 // kernels then serve the call), and its launch (hipErrorNotReady, with nothing launched,
 // without the buffers).
 bool cells_criterion_applies(const tsbts_ctx *c, int64_t n_act);
-bool cells_prepare(tsbts_ctx *c);
+bool cells_prepare(tsbts_ctx *c, hipStream_t st);
 hipError_t launch_timestep_cells(tsbts_ctx *c, const int32_t *idx, int n_act, double eta,
                                  double *dtc, hipStream_t st);
 

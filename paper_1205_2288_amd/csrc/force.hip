@@ -718,7 +718,8 @@ hipError_t run_scalar(ForceArgs &A, hipStream_t st) {
     chunk = A.share.chunk;
     A.n_jtiles = A.share.n_units;
     A.plan = A.share.plan;
-    A.fuse_reduce = A.plan.n_slices > 1 && A.plan.n_slices <= kShareFuse ? 1 : 0;
+    A.fuse_reduce =
+        A.share_done && A.plan.n_slices > 1 && A.plan.n_slices <= kShareFuse ? 1 : 0;
     A.done = A.share_done;
   } else {
     A.n_jtiles = static_cast<int>(A.snpad / chunk);
@@ -843,6 +844,15 @@ ShareShape share_step(const tsbts_ctx *c, int n_act) {
   return share_split(n_act, c->n, 0);
 }
 
+// A bound of the shared-target forms' partials over every active set, which a context
+// reserves so that no later call has to allocate: slices x targets is at most 2048 x 64 +
+// targets (share_split), and a slice holds at least one unit.
+int64_t share_partials_reserve(const tsbts_ctx *c) {
+  const int64_t k = std::min<int64_t>(c->n, kShareMaxAct);
+  const int64_t units = (c->n + kShare * kChunkTiny - 1) / (kShare * kChunkTiny);
+  return 4 * std::min<int64_t>(2048 * 64 + k, units * k);
+}
+
 int64_t force_partial_elems(const tsbts_ctx *c, int n_act, int blocks) {
   // small sets: one partial per j-tile and target
   if (n_act <= small_act_limit(c)) return c->npad / kTJ * 4 * n_act;
@@ -895,7 +905,8 @@ hipError_t launch_force_gather(tsbts_ctx *c, const int32_t *idx, int n_act, doub
   A.scalar_j = force_scalar_j(c) ? 1 : 0;
   A.chunk = scalar_chunk(c, n_act, 1);
   A.share = share_force(c, n_act);
-  A.share_done = share_done(c, 0);
+  // (calls on another array of partials may overlap the context's: no shared counts)
+  A.share_done = part == c->part ? share_done(c, 0) : nullptr;
   A.done = c->done;
   A.fuse_reduce = 0;
   if (src) {

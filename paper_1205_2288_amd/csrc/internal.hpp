@@ -78,8 +78,8 @@ struct tsbts_ctx {
                                                       // (mapped pinned memory)
   int32_t *idx_seen = nullptr;  // [n] occurrence counters of the check
   // finished-workgroup counts of the launches whose last workgroup reduces the partials
-  // (last_workgroup_partials), zero between launches: the small-set force [0] and criterion [1],
-  // then kShareTiles each for the tiles of 64 targets of the two (share_done)
+  // (last_workgroup_partials), zero between launches: the small-set force [0] and
+  // criterion [1], then kShareTiles each for the tiles of 64 targets of the two (share_done)
   uint32_t *done = nullptr;
   // symmetric all-targets kernels: work items (int4) and partials
   void *sym_items = nullptr;
@@ -437,6 +437,7 @@ inline uint32_t *share_done(const tsbts_ctx *c, int which) {
 }
 // The split of n_cols j-particles for n_targets (chunk 0: 64, or 16 for few).
 ShareShape share_split(int64_t n_targets, int64_t n_cols, int chunk);
+int64_t share_partials_reserve(const tsbts_ctx *c);
 ShareShape share_force(const tsbts_ctx *c, int n_act);
 ShareShape share_step(const tsbts_ctx *c, int n_act);
 // The criterion kernel likewise for large active sets (from 8192 targets, two targets per

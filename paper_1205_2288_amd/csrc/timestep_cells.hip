@@ -535,8 +535,12 @@ bool cells_criterion_applies(const tsbts_ctx *c, int64_t n_act) {
   return pairs >= kPairs + kTargets * c->n;
 }
 
-bool cells_prepare(tsbts_ctx *c) {
+bool cells_prepare(tsbts_ctx *c, hipStream_t st) {
   if (c->cell_buf) return true;
+  // a capture in progress cannot allocate: the other kernels serve it
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone) return false;
   CellBufs b;
   if (hipMalloc(&c->cell_buf, cell_layout(c, nullptr, &b)) != hipSuccess) {
     (void)hipGetLastError();

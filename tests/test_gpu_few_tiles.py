@@ -65,3 +65,35 @@ def test_tile_reductions(prec, sep, n, k):
         assert np.array_equal(a.cpu().numpy(), acc) and np.array_equal(d.cpu().numpy(), dtc)
         assert np.array_equal(ctx.force(idx, 0.0)[0].cpu().numpy(), acc)
     ctx.close()
+
+
+@pytest.mark.parametrize("prec,n,k", [("fp64", 4000, 1984), ("mixed", 4000, 1984),
+                                      ("fp64", 3000, 1500), ("fp64", 16384, 16384),
+                                      ("mixed", 16384, 9000)])
+def test_first_call_in_a_capture(prec, n, k):
+    # a context's first force, criterion and adjoint on a set, captured: the scratch was
+    # reserved, and what would allocate (the criterion's spatial order) is not taken
+    r, v, m = plummer(n, 7600 + n, masses="loguniform")
+    ctx = make_ctx(n, 1 / 256, prec)
+    ctx.bind(r, v, m)
+    ctx.predict(0.0)
+    idx = ctx.idx(np.random.default_rng(n).permutation(n)[:k].astype(np.int32))
+    new = lambda *s: torch.zeros(s, dtype=torch.float64, device="cuda")  # noqa: E731
+    a, d, gr, gm = new(3, k), new(k), new(3, n), new(n)
+    g = torch.cos(torch.arange(3 * k, dtype=torch.float64, device="cuda")).view(3, k)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        L.tsbts_force(ctx.ctx, idx, 0.0, a, None)
+        L.tsbts_timestep(ctx.ctx, idx, 0.1, d)
+        L.tsbts_force_backward(ctx.ctx, n, idx, 0.0, g, None, gr, gm)
+    for _ in range(3):
+        for x in (a, d, gr, gm):
+            x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        acc = ctx.force(idx, 0.0, with_pot=False)[0]
+        wr, wm = ctx.force_backward(idx, 0.0, g, None)
+        assert torch.equal(a, acc) and torch.equal(d, ctx.timestep(idx, 0.1))
+        assert torch.equal(gr, wr) and torch.equal(gm, wm)
+    ctx.close()
