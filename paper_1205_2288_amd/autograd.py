@@ -73,9 +73,31 @@ class _State:
         self.r, self.v, self.a = (flat[3 * n * c:3 * n * (c + 1)].view(3, n) for c in range(3))
         self.t_last, self.dt = flat[9 * n:10 * n], flat[10 * n:]
 
+    def _arrays(self):
+        return self.r, self.v, self.a, self.t_last, self.dt
+
     def bind(self, ctx: Context, m):
+        """The context's state is this one from here on; a context that binds copies of
+        what it is given (another device, a stand-in) has its own five arrays."""
+        given = self._arrays()
         ctx.bind(self.r, self.v, m, a=self.a, t_last=self.t_last, dt=self.dt)
+        self.r, self.v, self.a, self.t_last, self.dt = ctx.r, ctx.v, ctx.a, ctx.t_last, ctx.dt
+        self.whole = all(x.data_ptr() == y.data_ptr() for x, y in zip(given, self._arrays()))
         return self
+
+    def save(self):
+        if self.whole:
+            return self.flat.clone()
+        return torch.cat([x.reshape(-1) for x in self._arrays()])
+
+    def restore(self, flat):
+        if self.whole:
+            self.flat.copy_(flat)
+            return
+        done = 0
+        for x in self._arrays():
+            x.copy_(flat[done:done + x.numel()].view(x.shape))
+            done += x.numel()
 
     @classmethod
     def start(cls, ctx: Context, r0, v0, m, dt):
@@ -92,7 +114,7 @@ class _State:
 
     @classmethod
     def like(cls, ctx: Context, flat, m):
-        """A bound state of its own (its values come from a later copy to flat)."""
+        """A bound state of its own (its values come from a later restore)."""
         return cls(ctx, torch.empty_like(flat)).bind(ctx, m)
 
 
@@ -112,7 +134,7 @@ class TsbtsLeapfrog(torch.autograd.Function):
         checkpoints = []
         for s in range(steps):
             if s % era == 0:
-                checkpoints.append((s, st.flat.clone()))
+                checkpoints.append((s, st.save()))
             _step(ctx, every, acc, s, h)
         fctx.tsbts = ctx
         fctx.meta = (h, steps, era)
@@ -141,7 +163,7 @@ class TsbtsLeapfrog(torch.autograd.Function):
             s1 = min(s0 + era, steps)
             # recompute the era from its checkpoint, keeping the positions of every step;
             # the last step's are its prediction, its force is not needed
-            st.flat.copy_(flat)
+            st.restore(flat)
             pos = []
             for s in range(s0, s1 - 1):
                 _step(ctx, every, acc, s, h)
@@ -232,7 +254,7 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
         checkpoints = []
         for s in range(sched.K):
             if s % era == 0:
-                checkpoints.append((s, st.flat.clone()))
+                checkpoints.append((s, st.save()))
             _block_step(ctx, sched, s, buf)
         fctx.tsbts = ctx
         fctx.sched = sched
@@ -260,17 +282,17 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
         st = _State.like(ctx, first, m)
         for (s0, flat) in reversed(fctx.checkpoints):
             s1 = min(s0 + era, sched.K)
-            st.flat.copy_(flat)
+            st.restore(flat)
             # the states before the era's steps; the last one stays in place, and what its
             # step gives is not needed
             pre = [flat]
             for s in range(s0, s1 - 1):
                 if s > s0:
-                    pre.append(st.flat.clone())
+                    pre.append(st.save())
                 _block_step(ctx, sched, s, buf)
             for s in range(s1 - 1, s0 - 1, -1):
                 if s < s1 - 1:
-                    st.flat.copy_(pre[s - s0])
+                    st.restore(pre[s - s0])
                 tb = sched.time(s)
                 idx = sched.active(s)
                 k = idx.numel()
@@ -364,7 +386,7 @@ def _sched_pass(ctx: Context, st: _State, steps, buf, use_history: bool, record:
         ctx.history_begin()
     for (tb, idx, dtn) in steps:
         if pre is not None:
-            pre.append(st.flat.clone())
+            pre.append(st.save())
         k = idx.numel()
         acc = buf[:3 * k].view(3, k)
         ctx.predict(tb, use_history)
@@ -397,12 +419,12 @@ class TsbtsScheduleLeapfrog(torch.autograd.Function):
         ctx.force(every, 0.0, with_pot=False, acc=st.a)
         starts = []
         for passes in sched.eras:
-            start = st.flat.clone()
+            start = st.save()
             starts.append(start)
             ctx.history_clear()
             for p, steps in enumerate(passes):
                 if p:
-                    st.flat.copy_(start)
+                    st.restore(start)
                 _sched_pass(ctx, st, steps, buf, p > 0, p < len(passes) - 1,
                             dt_start=sched.pass_dt[len(starts) - 1][p])
         ctx.history_clear()
@@ -442,19 +464,19 @@ class TsbtsScheduleLeapfrog(torch.autograd.Function):
                 # interpolation source of pass p: pass p-1, rebuilt from the era start
                 ctx.history_clear()
                 for q in range(p):
-                    st.flat.copy_(start)
+                    st.restore(start)
                     _sched_pass(ctx, st, passes[q], buf, q > 0, True,
                                 dt_start=sched.pass_dt[e][q])
                 if p:
                     layout = ctx.history_layout()
                     hbar = torch.zeros((6, layout[0]), dtype=torch.float64, device=dev)
-                st.flat.copy_(start)
+                st.restore(start)
                 pre = []
                 _sched_pass(ctx, st, passes[p], buf, p > 0, False, pre,
                             dt_start=sched.pass_dt[e][p])
                 rb, vb, ab = (rbar, vbar, abar) if p == P - 1 else (z(), z(), z())
                 for s in range(len(passes[p]) - 1, -1, -1):
-                    st.flat.copy_(pre[s])
+                    st.restore(pre[s])
                     tb, idx, _ = passes[p][s]
                     k = idx.numel()
                     sd = seeds[:3 * k].view(3, k)
@@ -472,7 +494,7 @@ class TsbtsScheduleLeapfrog(torch.autograd.Function):
                 ctx.adjoint_accumulate(rb, vb, ab, acc_r, acc_v, acc_a)
                 later = (layout, hbar) if p else None
             rbar, vbar, abar = acc_r, acc_v, acc_a
-            st.flat.copy_(start)
+            st.restore(start)
         ctx.history_clear()
         ctx.load_positions(_State(ctx, first).r, m, 0.0)
         ctx.force_backward(fctx.every, 0.0, abar, None, rbar, mbar)   # through a_0
