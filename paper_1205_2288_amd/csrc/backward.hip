@@ -256,26 +256,6 @@ __global__ __launch_bounds__(kWG) void k_bwd_rows_reduce(BwdArgs A) {
   A.gm[k] += tot[3];
 }
 
-template <int SCALE_R>
-__global__ __launch_bounds__(kWG) void k_bwd_rows_reduce_wave(BwdArgs A) {
-  const int64_t k = static_cast<int64_t>(blockIdx.x) * (kWG / 64) + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (k >= A.n) return;
-  double tot[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int s = lane; s < A.plan.n_slices; s += 64) {
-    const double *in = A.part + static_cast<int64_t>(s) * 4 * A.n;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) tot[e] += in[e * A.n + k];
-  }
-#pragma unroll
-  for (int e = 0; e < 4; ++e) tot[e] = wave_sum(tot[e]);
-  if (lane != 0) return;
-  const double mk = SCALE_R ? A.p64[P64_M * A.npad + k] : 1.0;
-#pragma unroll
-  for (int e = 0; e < 3; ++e) A.gr[e * A.n + k] += mk * tot[e];
-  A.gm[k] += tot[3];
-}
-
 // Many slices, or few rows: a workgroup per 64 consecutive rows whose kRowsWaves waves each
 // add a contiguous range of the slices, as the force's reduction does (N = 8192, 32
 // slices: 10.4 -> 4.8 us).  NV = 4: the source or both parts' rows, k_bwd_rows_reduce's
@@ -716,15 +696,13 @@ bool reduce_by_rows(int n_slices, int64_t n_rows) {
                           use_rows_reduce(n_slices, n_rows));
 }
 
+// (more than kRowsFewSlices slices of all particles' rows need more particles than kFewRows)
 template <int SCALE_R>
 void reduce_rows(BwdArgs &A, hipStream_t st) {
   if (reduce_by_rows(A.plan.n_slices, A.n)) {
     const int nb = static_cast<int>((A.n + 63) / 64);
     hipLaunchKernelGGL((k_bwd_reduce_rows<4, SCALE_R>), dim3(nb), dim3(64 * kRowsWaves), 0, st,
                        A, static_cast<int>(A.n));
-  } else if (use_wave_reduce(A.plan.n_slices, A.n)) {
-    const int nb = static_cast<int>((A.n + kWG / 64 - 1) / (kWG / 64));
-    hipLaunchKernelGGL(k_bwd_rows_reduce_wave<SCALE_R>, dim3(nb), dim3(kWG), 0, st, A);
   } else if (A.plan.n_slices > 1) {
     const int nb = static_cast<int>((A.n + kWG - 1) / kWG);
     hipLaunchKernelGGL(k_bwd_rows_reduce<SCALE_R>, dim3(nb), dim3(kWG), 0, st, A);
