@@ -79,7 +79,7 @@ TRAFFIC_KIB = {
         "1d5043e8a01cc2c9"),
     "k_energy_pairs": (33877.6, 256.0,
         ("energy.hip", "internal.hpp"),
-        "6a52d9e8fe1fa423"),
+        "7043070b8cca35d7"),
 }
 
 

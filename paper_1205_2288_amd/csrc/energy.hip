@@ -1,7 +1,8 @@
 // Total energy E = K + W for the energy-error diagnostic (Section 3), in float64:
 //   K =  1/2 sum_i m_i |v_i|^2,   W = -sum_{i<j} m_i m_j (|r_i - r_j|^2 + eps^2)^(-1/2).
 // The upper triangle of 256x256 particle tiles (I <= J) is enumerated in row order and cut
-// into at most kMaxEB contiguous ranges of tile pairs, one per workgroup: for each pair,
+// into at most kMaxEB contiguous ranges of tile pairs (of parts of them where they are
+// few), one per workgroup: for each pair,
 // target i = 256 I + lane in registers, the sources of tile J through wave-uniform (scalar)
 // loads, and on diagonal tiles only j > i counts.  Each lane sums its pairs in range
 // order, the workgroup reduces its lanes in a fixed order into one partial, and a single
@@ -21,6 +22,16 @@ namespace {
 
 constexpr int kTE = 256;
 constexpr int64_t kMaxEB = 8192;  // workgroups (and partials) of the pair kernel
+// With few tile pairs each is cut into parts of its sources, up to kMaxParts and about
+// kPartItems items: a serial chain of 256 pairs per lane would set the time (us, whole
+// tile pairs and parts: N = 1000 24.6, 7.6; 4096 25.0, 12.8; 8192 36.5, 27.0).
+constexpr int64_t kPartItems = 4096;
+constexpr int kMaxPartBits = 3;
+int energy_part_bits(int64_t ntp) {
+  int q = 0;
+  while (q < kMaxPartBits && (2 * ntp << q) <= kPartItems) ++q;
+  return q;
+}
 
 struct EnergyArgs {
   int64_t n;
@@ -28,9 +39,10 @@ struct EnergyArgs {
   double eps2;
   int64_t T;       // tile rows
   int64_t ntp;     // tile pairs T (T + 1) / 2
-  int64_t nb;      // workgroups: min(ntp, kMaxEB)
+  int64_t nb;      // workgroups: min(ntp << part_bits, kMaxEB)
   double *part;    // [nb][2]
   double *out;
+  int part_bits;  // log2 of the parts of each tile pair's sources
 };
 
 // Tile pair b -> (I, J), I <= J, rows enumerated I = 0, 1, ... with T - I pairs each.
@@ -70,22 +82,25 @@ __global__ __launch_bounds__(kWG) void k_energy_pairs(EnergyArgs A) {
   __shared__ double red[2][kWG / 64];
   const int tid = threadIdx.x;
   const int64_t n = A.n;
-  // this workgroup's contiguous range of tile pairs
-  const int64_t b0 = blockIdx.x * A.ntp / A.nb, b1 = (blockIdx.x + 1) * A.ntp / A.nb;
+  // this workgroup's contiguous range of the parts of tile pairs
+  const int64_t items = A.ntp << A.part_bits;
+  const int64_t b0 = blockIdx.x * items / A.nb, b1 = (blockIdx.x + 1) * items / A.nb;
+  const int len = kTE >> A.part_bits;
   double pw = 0.0, pk = 0.0;
   for (int64_t b = b0; b < b1; ++b) {
     int64_t I, J;
-    tile_pair(b, A.T, I, J);
+    tile_pair(b >> A.part_bits, A.T, I, J);
+    const int part = static_cast<int>(b) & ((1 << A.part_bits) - 1);
     const int64_t i = I * kTE + tid;
     // targets past the last particle read its position and count for nothing
     const int64_t ii = i < n ? i : n - 1;
     const double xi = A.r[ii], yi = A.r[n + ii], zi = A.r[2 * n + ii];
     const double mi = i < n ? A.m[ii] : 0.0;
-    if (I == J) {
+    if (I == J && part == 0) {
       const double vx = A.v[ii], vy = A.v[n + ii], vz = A.v[2 * n + ii];
       pk += 0.5 * mi * (vx * vx + vy * vy + vz * vz);
     }
-    const int64_t j0 = J * kTE, j1 = j0 + kTE < n ? j0 + kTE : n;
+    const int64_t j0 = J * kTE + part * len, j1 = j0 + len < n ? j0 + len : n;
     const double w = I != J ? energy_tile<0>(A, j0, j1, i, xi, yi, zi)
                             : energy_tile<1>(A, j0, j1, i, xi, yi, zi);
     // (a target past the last particle may have met itself at no distance)
@@ -138,7 +153,8 @@ __global__ __launch_bounds__(kRedWG) void k_energy_reduce(EnergyArgs A) {
 
 int64_t energy_partials_needed(const tsbts_ctx *c) {
   const int64_t T = (c->n + kTE - 1) / kTE;
-  return 2 * std::min<int64_t>(T * (T + 1) / 2, kMaxEB);  // two doubles per workgroup
+  const int64_t ntp = T * (T + 1) / 2;
+  return 2 * std::min<int64_t>(ntp << energy_part_bits(ntp), kMaxEB);  // two per workgroup
 }
 
 hipError_t launch_energy(tsbts_ctx *c, const double *r, const double *v, const double *m,
@@ -151,7 +167,8 @@ hipError_t launch_energy(tsbts_ctx *c, const double *r, const double *v, const d
   A.eps2 = c->eps * c->eps;
   A.T = (c->n + kTE - 1) / kTE;
   A.ntp = A.T * (A.T + 1) / 2;
-  A.nb = std::min<int64_t>(A.ntp, kMaxEB);
+  A.part_bits = energy_part_bits(A.ntp);
+  A.nb = std::min<int64_t>(A.ntp << A.part_bits, kMaxEB);
   A.part = c->epart;
   A.out = out;
   hipLaunchKernelGGL(k_energy_pairs, dim3(static_cast<unsigned>(A.nb)), dim3(kWG), 0, st, A);

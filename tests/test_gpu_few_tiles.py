@@ -97,3 +97,17 @@ def test_first_call_in_a_capture(prec, n, k):
         assert torch.equal(a, acc) and torch.equal(d, ctx.timestep(idx, 0.1))
         assert torch.equal(gr, wr) and torch.equal(gm, wm)
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 31, 33, 255, 257, 700, 2000, 5633, 7936, 11500])
+def test_energy_of_few_tiles(n):
+    # each split of the tile pairs (8, 4, 2 and 1 parts), tails inside a part; float64 sums
+    # of n (n - 1) / 2 terms of one sign: 1e-13 relative leaves sqrt(n^2) roundings ample room
+    r, v, m = plummer(n, 7700 + n, masses="loguniform")
+    ctx = make_ctx(n, 1 / 64, "fp64")
+    ctx.bind(r, v, m)
+    kin, pot = ctx.energy().cpu().numpy()
+    ctx.close()
+    phi = oracle.force(r, m, 1 / 64, np.arange(n, dtype=np.int32))[1]
+    assert kin == pytest.approx(0.5 * (m * (v * v).sum(0)).sum(), rel=1e-13)
+    assert pot == pytest.approx(0.5 * (m * phi).sum(), rel=1e-13)
