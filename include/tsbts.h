@@ -199,7 +199,8 @@ int tsbts_force(tsbts_ctx *ctx, const int32_t *active_idx, int32_t n_active, dou
  * Every call on one GPU shares that GPU's array and leaves its partials there (each value
  * a call reads is written earlier in the same call, so nothing needs clearing): calls
  * that overlap on one GPU (other streams, contexts or host threads) race and give
- * undefined results; serialise them. */
+ * undefined results; serialise them.  They may overlap the context's other force and
+ * criterion calls, which read the same predicted arrays. */
 int tsbts_force_noalloc(tsbts_ctx *ctx, const int32_t *active_idx, int32_t n_active,
                         double t_block, double *acc, double *pot, hipStream_t stream);
 

@@ -251,10 +251,10 @@ int tsbts_create(tsbts_ctx **out, int64_t n, double eps, int precision, int flag
   if (!st) st = dev_alloc(c, &c->h.tsum, (n + 8191) / 8192);
   if (!st) st = dev_alloc(c, &c->h.off, n + 1);
   if (!st) st = dev_alloc(c, &c->h.cur, n);
-  if (!st) st = dev_alloc(c, &c->done, 2 + 2 * kShareTiles);
+  if (!st) st = dev_alloc(c, &c->done, kDoneCounts);
   // zero before any launch on any of the caller's streams (which may not wait for the
   // null stream)
-  if (!st && (hipMemset(c->done, 0, (2 + 2 * kShareTiles) * sizeof(uint32_t)) != hipSuccess ||
+  if (!st && (hipMemset(c->done, 0, kDoneCounts * sizeof(uint32_t)) != hipSuccess ||
               hipDeviceSynchronize() != hipSuccess)) {
     (void)hipGetLastError();
     st = TSBTS_EHIP;

@@ -907,7 +907,7 @@ hipError_t launch_force_gather(tsbts_ctx *c, const int32_t *idx, int n_act, doub
   A.share = share_force(c, n_act);
   // (calls on another array of partials may overlap the context's: no shared counts)
   A.share_done = part == c->part ? share_done(c, 0) : nullptr;
-  A.done = c->done;
+  A.done = force_done(c, part);
   A.fuse_reduce = 0;
   if (src) {
     // the scalar-load kernel over the given sources with a target per lane of the
@@ -983,7 +983,7 @@ hipError_t launch_force_predicted(tsbts_ctx *c, const int32_t *idx, int n_act, d
   A.ipl = 1;
   A.scalar_j = 0;
   A.chunk = kTJ;
-  A.done = c->done;
+  A.done = force_done(c, c->part);
   A.fuse_reduce = 0;
   PredictArgs P = predict_args(c, t_block, use_history);
   set_pending(P, pend);

@@ -78,8 +78,7 @@ struct tsbts_ctx {
                                                       // (mapped pinned memory)
   int32_t *idx_seen = nullptr;  // [n] occurrence counters of the check
   // finished-workgroup counts of the launches whose last workgroup reduces the partials
-  // (last_workgroup_partials), zero between launches: the small-set force [0] and
-  // criterion [1], then kShareTiles each for the tiles of 64 targets of the two (share_done)
+  // (last_workgroup_partials), zero between launches (force_done, step_done, share_done)
   uint32_t *done = nullptr;
   // symmetric all-targets kernels: work items (int4) and partials
   void *sym_items = nullptr;
@@ -432,8 +431,18 @@ struct ShareShape {
   int n_units;     // units of kShare * chunk (the last one may pass the padding)
   SplitPlan plan;  // n_itiles counts 64 targets
 };
+// Finished-workgroup counts: one for each launch that may overlap another on the context.
+// The small-set force counts apart when its partials lie in another array than the
+// context's (the fixed one), whose calls the caller need not order with the context's; the
+// small-set criterion; then each tile of 64 targets of the force (which = 0) and the
+// criterion (1).
+constexpr int kDoneCounts = 3 + 2 * kShareTiles;
+inline uint32_t *force_done(const tsbts_ctx *c, const double *part) {
+  return c->done + (part == c->part ? 0 : 2);
+}
+inline uint32_t *step_done(const tsbts_ctx *c) { return c->done + 1; }
 inline uint32_t *share_done(const tsbts_ctx *c, int which) {
-  return c->done + 2 + which * kShareTiles;
+  return c->done + 3 + which * kShareTiles;
 }
 // The split of n_cols j-particles for n_targets (chunk 0: 64, or 16 for few).
 ShareShape share_split(int64_t n_targets, int64_t n_cols, int chunk);

@@ -468,7 +468,7 @@ StepArgs gather_args(tsbts_ctx *c, const int32_t *idx, int n_act, double eta, do
   A.share_done = share_done(c, 1);
   A.scalar_j = A.share.chunk || criterion_scalar_j(c, n_act) ? 1 : 0;
   A.chunk = scalar_chunk(c, n_act, A.ipl);
-  A.done = c->done + 1;
+  A.done = step_done(c);
   A.fuse_reduce = 0;
   return A;
 }

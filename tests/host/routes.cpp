@@ -1,0 +1,34 @@
+// The library's host-side rules (which kernel form, split, reduction and counter a call
+// takes) behind a C interface, on a context that only has the fields the rules read.
+#include "cells.hpp"
+#include "internal.hpp"
+
+using namespace tsbts;
+
+extern "C" {
+
+tsbts_ctx *route_ctx(int64_t n, int precision) {
+  tsbts_ctx *c = new tsbts_ctx();
+  c->n = n;
+  c->npad = round_up(n, kPad);
+  c->precision = precision;
+  // never read or written: the rules only compare and offset these
+  c->part = reinterpret_cast<double *>(0x10000);
+  c->done = reinterpret_cast<uint32_t *>(0x20000);
+  return c;
+}
+void route_free(tsbts_ctx *c) { delete c; }
+
+// Counter of a small-set force call with partials in the context's array or another, and of
+// a small-set criterion call, as offsets.
+int route_force_done(const tsbts_ctx *c, int own) {
+  double *part = own ? c->part : c->part + 1;
+  return static_cast<int>(force_done(c, part) - c->done);
+}
+int route_step_done(const tsbts_ctx *c) { return static_cast<int>(step_done(c) - c->done); }
+int route_share_done(const tsbts_ctx *c, int which) {
+  return static_cast<int>(share_done(c, which) - c->done);
+}
+int route_done_counts() { return kDoneCounts; }
+int route_share_tiles() { return kShareTiles; }
+}

@@ -1,0 +1,62 @@
+"""Host-side rules of the library (CPU tier): which counters, kernel forms and reductions a
+call takes, through tests/host/routes.cpp."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+PKG = os.path.join(ROOT, "paper_1205_2288_amd")
+HIPCC = "/opt/rocm/bin/hipcc"
+FP64, MIXED = 0, 1
+
+
+@pytest.fixture(scope="module")
+def routes(tmp_path_factory):
+    lib = os.path.join(PKG, "libtsbts.so")
+    if not os.path.exists(HIPCC) or not os.path.exists(lib):
+        pytest.skip("hipcc or the built library not available")
+    out = str(tmp_path_factory.mktemp("routes") / "libroutes.so")
+    res = subprocess.run([HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17",
+                          "-fPIC", "-shared", "-I", os.path.join(PKG, "csrc"),
+                          os.path.join(ROOT, "tests", "host", "routes.cpp"), "-o", out,
+                          "-L", PKG, "-ltsbts", f"-Wl,-rpath,{PKG}"],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-3000:]
+    r = ctypes.CDLL(out)
+    r.route_ctx.restype = ctypes.c_void_p
+    r.route_ctx.argtypes = [ctypes.c_int64, ctypes.c_int]
+    for name in ("route_free", "route_step_done"):
+        getattr(r, name).argtypes = [ctypes.c_void_p]
+    for name in ("route_force_done", "route_share_done"):
+        getattr(r, name).argtypes = [ctypes.c_void_p, ctypes.c_int]
+    return r
+
+
+@pytest.fixture
+def make(routes):
+    made = []
+
+    def ctx(n, precision):
+        made.append(routes.route_ctx(n, precision))
+        return made[-1]
+
+    yield ctx
+    for c in made:
+        routes.route_free(c)
+
+
+def test_calls_that_may_overlap_count_apart(routes, make):
+    # a force call whose partials are in the fixed array may overlap the context's own
+    # force call: each of the two, the criterion and every tile of the shared forms has a
+    # counter of its own, all inside the allocation
+    c = make(4096, MIXED)
+    tiles = routes.route_share_tiles()
+    used = [routes.route_force_done(c, 1), routes.route_force_done(c, 0),
+            routes.route_step_done(c)]
+    for which in (0, 1):
+        first = routes.route_share_done(c, which)
+        used += range(first, first + tiles)
+    assert len(set(used)) == len(used)
+    assert min(used) >= 0 and max(used) < routes.route_done_counts()
