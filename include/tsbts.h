@@ -121,7 +121,11 @@ int tsbts_destroy(tsbts_ctx *ctx);
  * (n (2 k - 1300) in float64) runs over a spatial order of the particles that leaves out
  * pairs which cannot change a target's extremes (the same values bit for bit).  The first
  * such call on a context allocates a few hundred bytes per particle; where that fails, or
- * while its stream is captured, the other kernels serve it.
+ * while its stream is captured, the other kernels serve it.  A captured tsbts_timestep of
+ * more than 32 targets allocates nothing: without the buffers of the spatial order, of the
+ * symmetric kernels or of a split call, which an earlier call would have left, the gather
+ * kernels serve it (a context tuned to more workgroups than the default may allocate).  The
+ * other calls that are said to allocate here cannot be captured as a context's first.
  * Results do not depend on these except through the order of float64 tile sums.
  * Invalid values return TSBTS_EINVAL and leave the setting unchanged. */
 int tsbts_tune(tsbts_ctx *ctx, int param, int value);

@@ -264,8 +264,8 @@ int tsbts_create(tsbts_ctx **out, int64_t n, double eps, int precision, int flag
     st = dev_alloc(c, &c->epart, c->epart_cap);
   }
   if (!st) {
-    const int64_t need = std::max({partial_elems_needed(c, static_cast<int>(n)),
-                                   backward_partials_reserve(c), share_partials_reserve(c),
+    const int64_t need = std::max({gather_partials_reserve(c), backward_partials_reserve(c),
+                                   share_partials_reserve(c),
                                    fused_partials_needed(c, static_cast<int>(n))});
     st = ensure_part(c, need);
   }
@@ -532,16 +532,20 @@ int tsbts_timestep(tsbts_ctx *c, const int32_t *idx, int32_t n_act, double eta, 
   if (!dtc) return fail(c, TSBTS_EINVAL, "dtc is NULL");
   if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, TSBTS_EINVAL, "eta must be > 0");
   if (!c->have_pred) return fail(c, TSBTS_ESTATE, "no predicted particle arrays");
-  // without the buffers of the spatial order the other kernels serve the call
+  // without the buffers of the spatial order the other kernels serve the call; a captured
+  // call allocates nothing (the gather kernels' partials were reserved) and takes the forms
+  // whose buffers are there
   if (!cells_criterion_applies(c, n_act) || !cells_prepare(c, stream)) {
     if (int s = ensure_part(c, partial_elems_needed(c, n_act))) return s;
-    if (criterion_sym_applies(c, n_act)) {
-      const int vb = c->precision == TSBTS_FP64 ? 8 : 4;
-      if (int s = sym_prepare(c, 2, vb, vb))
-        return fail(c, s, "symmetric criterion: work list or partials not allocated");
+    if (may_allocate(stream)) {
+      if (criterion_sym_applies(c, n_act)) {
+        const int vb = c->precision == TSBTS_FP64 ? 8 : 4;
+        if (int s = sym_prepare(c, 2, vb, vb))
+          return fail(c, s, "symmetric criterion: work list or partials not allocated");
+      }
+      if (int s = split_prepare(c, n_act))
+        return fail(c, s, "split call: buffers not allocated");
     }
-    if (int s = split_prepare(c, n_act))
-      return fail(c, s, "split call: buffers not allocated");
   }
   hipError_t e = launch_timestep(c, idx, n_act, eta, dtc, stream);
   if (e != hipSuccess) return hip_fail(c, e, "tsbts_timestep launch");

@@ -447,6 +447,10 @@ inline uint32_t *share_done(const tsbts_ctx *c, int which) {
 // The split of n_cols j-particles for n_targets (chunk 0: 64, or 16 for few).
 ShareShape share_split(int64_t n_targets, int64_t n_cols, int chunk);
 int64_t share_partials_reserve(const tsbts_ctx *c);
+int64_t gather_partials_reserve(const tsbts_ctx *c);
+// Whether a call on this stream may allocate: not while the stream is captured, nor when
+// that cannot be told (the legacy stream during another stream's capture).
+bool may_allocate(hipStream_t st);
 ShareShape share_force(const tsbts_ctx *c, int n_act);
 ShareShape share_step(const tsbts_ctx *c, int n_act);
 // The criterion kernel likewise for large active sets (from 8192 targets, two targets per

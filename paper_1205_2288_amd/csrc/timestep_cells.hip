@@ -537,10 +537,7 @@ bool cells_criterion_applies(const tsbts_ctx *c, int64_t n_act) {
 
 bool cells_prepare(tsbts_ctx *c, hipStream_t st) {
   if (c->cell_buf) return true;
-  // a capture in progress cannot allocate: the other kernels serve it
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
-  if (capture != hipStreamCaptureStatusNone) return false;
+  if (!may_allocate(st)) return false;  // the other kernels serve a captured call
   CellBufs b;
   if (hipMalloc(&c->cell_buf, cell_layout(c, nullptr, &b)) != hipSuccess) {
     (void)hipGetLastError();

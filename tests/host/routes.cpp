@@ -1,5 +1,7 @@
 // The library's host-side rules (which kernel form, split, reduction and counter a call
 // takes) behind a C interface, on a context that only has the fields the rules read.
+#include <algorithm>
+
 #include "cells.hpp"
 #include "internal.hpp"
 
@@ -31,4 +33,11 @@ int route_share_done(const tsbts_ctx *c, int which) {
 }
 int route_done_counts() { return kDoneCounts; }
 int route_share_tiles() { return kShareTiles; }
+}
+
+extern "C" {
+int64_t route_partials(const tsbts_ctx *c, int k) { return partial_elems_needed(c, k); }
+int64_t route_reserve(const tsbts_ctx *c) {
+  return std::max(gather_partials_reserve(c), share_partials_reserve(c));
+}
 }

@@ -27,9 +27,11 @@ def routes(tmp_path_factory):
     r = ctypes.CDLL(out)
     r.route_ctx.restype = ctypes.c_void_p
     r.route_ctx.argtypes = [ctypes.c_int64, ctypes.c_int]
-    for name in ("route_free", "route_step_done"):
+    for name in ("route_free", "route_step_done", "route_reserve"):
         getattr(r, name).argtypes = [ctypes.c_void_p]
-    for name in ("route_force_done", "route_share_done"):
+    for name in ("route_reserve", "route_partials"):
+        getattr(r, name).restype = ctypes.c_int64
+    for name in ("route_force_done", "route_share_done", "route_partials"):
         getattr(r, name).argtypes = [ctypes.c_void_p, ctypes.c_int]
     return r
 
@@ -60,3 +62,15 @@ def test_calls_that_may_overlap_count_apart(routes, make):
         used += range(first, first + tiles)
     assert len(set(used)) == len(used)
     assert min(used) >= 0 and max(used) < routes.route_done_counts()
+
+
+@pytest.mark.parametrize("precision", [FP64, MIXED])
+@pytest.mark.parametrize("n", [33, 500, 4096, 16384, 40000, 50000, 131072, 300000])
+def test_partials_of_every_active_set_are_reserved(routes, make, precision, n):
+    # no force or criterion call of the gather kernels above the small sets has to allocate
+    # (a captured one cannot): the reserve covers every active set, not all particles alone
+    c = make(n, precision)
+    reserve = routes.route_reserve(c)
+    step = max(1, n // 3000)
+    for k in [*range(33, min(n, 4200) + 1), *range(33, n + 1, step), n]:
+        assert routes.route_partials(c, k) <= reserve, k
