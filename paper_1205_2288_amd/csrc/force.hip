@@ -691,7 +691,7 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_force_reduce_rows(ForceArgs
 // The split-j reduction launch that suits the call (none when the j-range is not split).
 template <class V, int NEWTON>
 hipError_t launch_reduce(ForceArgs &A, hipStream_t st) {
-  if (use_rows_reduce(A.plan.n_slices, A.n_act)) {
+  if (force_rows_reduce(A.plan.n_slices, A.n_act, A.share.chunk != 0)) {
     const int nb = (A.n_act + 63) / 64;
     hipLaunchKernelGGL((k_force_reduce_rows<V, NEWTON>), dim3(nb), dim3(64 * kRowsWaves), 0, st,
                        A);
@@ -758,6 +758,7 @@ hipError_t run(ForceArgs &A, hipStream_t st) {
 template <class V, int NEWTON>
 hipError_t run_small(ForceArgs &A, hipStream_t st, const PredictArgs *pred = nullptr,
                      const InlineIdx *in = nullptr) {
+  A.share.chunk = 0;
   A.n_jtiles = A.used_tiles;
   A.plan.n_itiles = 1;
   A.plan.n_slices = A.n_jtiles;

@@ -321,13 +321,34 @@ __host__ __device__ inline bool use_wave_reduce(int n_slices, int64_t n_targets)
 // wave-per-target form touches a cache line per 8-byte partial).  Below that there are
 // too few such workgroups (at 256 targets 4, each wave walking 128 slices: 43 against
 // 34 us per call at N = 131072).
-// With at most kRowsFewSlices slices a wave walks few of them whatever the target count.
+// With at most kRowsFewSlices slices a wave walks few of them, and it pays from fewer
+// targets on: always for the kernels whose waves share 64 targets, whose slices are that
+// few; for the other forms from kRowsFewForce targets of the force (1500 of N = 16384, 64
+// slices, 30.7 -> 27.8 us a call; 500 of N = 4096, 64 slices, 9.6 -> 10.4) and kRowsFewStep
+// of the criterion (1500 28.4 -> 25.5, 500 12.5 -> 11.9), there from kRowsTinyStep where
+// there are kRowsTinySlices at most (16 of N = 20011, 79 slices, 8.1 -> 7.9; of N = 32768,
+// 128 slices, 8.1 -> 8.6).  Few targets are one such workgroup, whose waves would walk all
+// slices: one target's force at N = 60000, 235 slices, 5.1 us with a wave per target, 11.0
+// with rows.
 constexpr int64_t kRowsReduceMinTargets = 2048;
 constexpr int kRowsWaves = 16;
 constexpr int kRowsFewSlices = 256;
-__host__ __device__ inline bool use_rows_reduce(int n_slices, int64_t n_targets) {
+constexpr int kRowsFewForce = 1024, kRowsFewStep = 33;
+constexpr int kRowsTinyStep = 4, kRowsTinySlices = 96;
+__host__ __device__ inline bool use_rows_reduce(int n_slices, int64_t n_targets,
+                                                int64_t few = kRowsReduceMinTargets) {
   return n_slices >= kWaveReduceSlices &&
-         (n_targets >= kRowsReduceMinTargets || n_slices <= kRowsFewSlices);
+         (n_targets >= kRowsReduceMinTargets ||
+          (n_slices <= kRowsFewSlices && n_targets >= few));
+}
+__host__ __device__ inline bool force_rows_reduce(int n_slices, int64_t n_targets,
+                                                  bool shared) {
+  return use_rows_reduce(n_slices, n_targets, shared ? 1 : kRowsFewForce);
+}
+__host__ __device__ inline bool step_rows_reduce(int n_slices, int64_t n_targets,
+                                                 bool shared) {
+  return use_rows_reduce(n_slices, n_targets,
+                         shared ? 1 : n_slices <= kRowsTinySlices ? kRowsTinyStep : kRowsFewStep);
 }
 
 // The small-set kernels' last workgroup reduces the partials (W values per slice) itself

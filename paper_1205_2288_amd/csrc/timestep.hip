@@ -382,6 +382,7 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_timestep_reduce_rows(StepAr
 template <class V>
 hipError_t run(StepArgs &A, hipStream_t st) {
   if (A.n_act <= kSmallAct) {
+    A.share.chunk = 0;
     A.n_jtiles = static_cast<int>((A.n + kTJ - 1) / kTJ);  // without padding alone
     A.plan.n_itiles = 1;
     A.plan.n_slices = A.n_jtiles;
@@ -430,7 +431,7 @@ hipError_t run(StepArgs &A, hipStream_t st) {
     else
       hipLaunchKernelGGL((k_timestep<V, 1>), dim3(A.plan.nblk), dim3(kWG), 0, st, A);
   }
-  if (use_rows_reduce(A.plan.n_slices, A.n_act)) {
+  if (step_rows_reduce(A.plan.n_slices, A.n_act, A.share.chunk != 0)) {
     const int nb = (A.n_act + 63) / 64;
     hipLaunchKernelGGL(k_timestep_reduce_rows, dim3(nb), dim3(64 * kRowsWaves), 0, st, A);
   } else if (use_wave_reduce(A.plan.n_slices, A.n_act)) {

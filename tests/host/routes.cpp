@@ -41,3 +41,12 @@ int64_t route_reserve(const tsbts_ctx *c) {
   return std::max(gather_partials_reserve(c), share_partials_reserve(c));
 }
 }
+
+extern "C" {
+int route_force_rows(int slices, int64_t targets, int shared) {
+  return force_rows_reduce(slices, targets, shared != 0) ? 1 : 0;
+}
+int route_step_rows(int slices, int64_t targets, int shared) {
+  return step_rows_reduce(slices, targets, shared != 0) ? 1 : 0;
+}
+}

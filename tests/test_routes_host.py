@@ -27,6 +27,8 @@ def routes(tmp_path_factory):
     r = ctypes.CDLL(out)
     r.route_ctx.restype = ctypes.c_void_p
     r.route_ctx.argtypes = [ctypes.c_int64, ctypes.c_int]
+    for name in ("route_force_rows", "route_step_rows"):
+        getattr(r, name).argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int]
     for name in ("route_free", "route_step_done", "route_reserve"):
         getattr(r, name).argtypes = [ctypes.c_void_p]
     for name in ("route_reserve", "route_partials"):
@@ -74,3 +76,20 @@ def test_partials_of_every_active_set_are_reserved(routes, make, precision, n):
     step = max(1, n // 3000)
     for k in [*range(33, min(n, 4200) + 1), *range(33, n + 1, step), n]:
         assert routes.route_partials(c, k) <= reserve, k
+
+
+def test_few_targets_are_reduced_by_waves(routes):
+    # 65 to 256 slices of up to 32 targets (N = 16641 to 65536): a wave per target, not one
+    # workgroup for all of them
+    force, step = routes.route_force_rows, routes.route_step_rows
+    for slices in (65, 128, 256, 257):
+        for targets in (1, 8, 32, 64, 500, 1023):
+            assert not force(slices, targets, 0)
+        for targets in (1, 2, 3):
+            assert not step(slices, targets, 0)
+        assert force(slices, 2048, 0) and step(slices, 2048, 0)
+    for targets in (4, 16, 32):
+        assert not step(128, targets, 0) and step(65, targets, 0)
+    for rows in (force, step):
+        assert rows(128, 1024, 0) and not rows(257, 1024, 0)
+        assert rows(128, 33, 1) and not rows(257, 33, 1) and not rows(15, 5000, 1)
