@@ -117,8 +117,9 @@ int tsbts_destroy(tsbts_ctx *ctx);
  *                      a repeated index leaves undefined output rows when every particle
  *                      is a target and the symmetric kernels serve the call, or when a
  *                      split call does).
- * With all of these automatic, a criterion call of k targets with n (k - 1300) >= 9.4e7
- * (n (2 k - 1300) in float64) runs over a spatial order of the particles that leaves out
+ * With all of these automatic, a criterion call of k targets with n (k - 1300) >= 9.4e7 (in
+ * float64 n (2 k - 1300) from 4096 targets, below that n (k - 900) >= 6.0e7 or k >= 860 with
+ * n >= 2^19) runs over a spatial order of the particles that leaves out
  * pairs which cannot change a target's extremes (the same values bit for bit).  The first
  * such call on a context allocates a few hundred bytes per particle; where that fails, or
  * while its stream is captured, the other kernels serve it.  A captured tsbts_timestep of

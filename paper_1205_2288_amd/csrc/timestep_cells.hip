@@ -525,13 +525,27 @@ bool cells_criterion_applies(const tsbts_ctx *c, int64_t n_act) {
   // a call tuned to a kernel form keeps it
   if (c->tune_sym != 2 || c->tune_split != 2 || !force_scalar_j(c) || c->tune_chunk != 0)
     return false;
-  // The order and the tests take as long as kPairs pairs and kTargets targets of the
-  // gather kernels (half as many in float64).  Measured (us, mixed, this / gather): N =
-  // 131072 k = 2048 153 / 170; 65536 2048 106 / 94, 4096 103 / 166; 32768 4096 82 / 90;
-  // 16384 4096 71 / 53, 8192 74 / 88; 8192 8192 66 / 53.  Float64: N = 131072 k = 1024
-  // 157 / 145; 32768 2048 82 / 80; 16384 4096 73 / 77; 8192 8192 71 / 78.
+  // The order and the tests take as long as kPairs pairs and kTargets targets of the gather
+  // kernels (half as many in float64 from kShareMaxAct targets).  Measured either side of
+  // the line (us, this / gather): mixed N = 16384 k = 7061 72 / 71, 7300 70 / 78; 32768 4023
+  // 79 / 74, 4280 79 / 87; 65536 2669 105 / 108, 2840 100 / 117; 131072 1992 153 / 157, 2120
+  // 156 / 170; 262144 1500 238 / 214, 1661 241 / 248; 524288 1485 415 / 427, 1580 427 / 483;
+  // 1048576 1100 786 / 635, 1391 763 / 774.  Float64 N = 8400 k = 6643 71 / 67, 7834 68 / 85;
+  // 12000 4857 70 / 66, 5406 66 / 77; 18000 4351 71 / 84.
   constexpr int64_t kPairs = int64_t(90) << 20, kTargets = 1300;
-  const int64_t pairs = n_act * c->n * (c->precision == TSBTS_FP64 ? 2 : 1);
+  // Below kShareMaxAct targets the float64 gather kernels (waves share the targets) are
+  // faster, and the line lies higher; for many particles it flattens.  Measured: N = 16384
+  // k = 3953 67 / 59; 20011 3759 75 / 72, 4000 72 / 72; 32768 2600 83 / 78, 2804 83 / 85;
+  // 65536 1700 109 / 103, 1892 108 / 114; 131072 1200 163 / 135, 1436 153 / 164; 262144 1000
+  // 255 / 209, 1135 243 / 256; 524288 800 422 / 404, 900 420 / 441; 1048576 650 769 / 667, 850
+  // 746 / 839.
+  constexpr int64_t kPairs64 = 60000000, kTargets64 = 900;
+  constexpr int64_t kMany = int64_t(1) << 19, kManyTargets64 = 860;
+  const bool fp64 = c->precision == TSBTS_FP64;
+  if (fp64 && n_act < kShareMaxAct)
+    return n_act * c->n >= kPairs64 + kTargets64 * c->n ||
+           (c->n >= kMany && n_act >= kManyTargets64);
+  const int64_t pairs = n_act * c->n * (fp64 ? 2 : 1);
   return pairs >= kPairs + kTargets * c->n;
 }
 

@@ -50,3 +50,7 @@ int route_step_rows(int slices, int64_t targets, int shared) {
   return step_rows_reduce(slices, targets, shared != 0) ? 1 : 0;
 }
 }
+
+extern "C" int route_cells(const tsbts_ctx *c, int64_t k) {
+  return cells_criterion_applies(c, k) ? 1 : 0;
+}

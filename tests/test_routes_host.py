@@ -33,6 +33,7 @@ def routes(tmp_path_factory):
         getattr(r, name).argtypes = [ctypes.c_void_p]
     for name in ("route_reserve", "route_partials"):
         getattr(r, name).restype = ctypes.c_int64
+    r.route_cells.argtypes = [ctypes.c_void_p, ctypes.c_int64]
     for name in ("route_force_done", "route_share_done", "route_partials"):
         getattr(r, name).argtypes = [ctypes.c_void_p, ctypes.c_int]
     return r
@@ -93,3 +94,25 @@ def test_few_targets_are_reduced_by_waves(routes):
     for rows in (force, step):
         assert rows(128, 1024, 0) and not rows(257, 1024, 0)
         assert rows(128, 33, 1) and not rows(257, 33, 1) and not rows(15, 5000, 1)
+
+
+# (particles, targets) at which the gather kernels take less than 0.95 of the time of the
+# spatial order's, and at which they take more than 1.05 of it
+GATHER = {MIXED: [(16384, 4096), (32768, 3600), (65536, 2048), (131072, 1500), (262144, 1200),
+                  (524288, 1200), (1048576, 1100)],
+          FP64: [(8192, 4096), (16384, 3533), (16384, 3953), (20011, 3549), (32768, 2091),
+                 (65536, 1371), (131072, 1011), (131072, 1024), (131072, 1200), (262144, 831),
+                 (262144, 1000), (524288, 741), (1048576, 696)]}
+ORDER = {MIXED: [(16384, 9000), (32768, 5000), (65536, 3300), (131072, 2300), (262144, 1900),
+                 (524288, 1700), (1048576, 1600)],
+         FP64: [(9000, 7837), (12000, 5406), (16384, 4412), (20011, 4271), (45000, 2446),
+                (65536, 2048), (131072, 1522), (262144, 1280), (524288, 1100),
+                (1048576, 900)]}
+
+
+@pytest.mark.parametrize("precision", [FP64, MIXED])
+def test_spatial_order_serves_where_it_is_faster(routes, make, precision):
+    for n, k in GATHER[precision]:
+        assert not routes.route_cells(make(n, precision), k), (n, k)
+    for n, k in ORDER[precision]:
+        assert routes.route_cells(make(n, precision), k), (n, k)
