@@ -121,7 +121,8 @@ int tsbts_destroy(tsbts_ctx *ctx);
  * float64 n (2 k - 1300) from 4096 targets, below that n (k - 900) >= 6.0e7 or k >= 860 with
  * n >= 2^19) runs over a spatial order of the particles that leaves out
  * pairs which cannot change a target's extremes (the same values bit for bit).  The first
- * such call on a context allocates a few hundred bytes per particle; where that fails, or
+ * such call on a context (tsbts_timestep, or a combined call that runs the criterion's own
+ * kernels) allocates a few hundred bytes per particle; where that fails, from then on, or
  * while its stream is captured, the other kernels serve it.  A captured tsbts_timestep of
  * more than 32 targets allocates nothing: without the buffers of the spatial order, of the
  * symmetric kernels or of a split call, which an earlier call would have left, the gather

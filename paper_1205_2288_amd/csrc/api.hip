@@ -479,6 +479,7 @@ int tsbts_force_criterion(tsbts_ctx *c, const int32_t *idx, int32_t n_act, doubl
     // criterion first, on the same predicted state (same definition as the fused pass,
     // fewer idle lanes)
     if (int s = ensure_part(c, partial_elems_needed(c, n_act))) return s;
+    if (cells_criterion_applies(c, n_act)) (void)cells_prepare(c, stream);
     e = launch_timestep(c, idx, n_act, eta, dtc, stream);
     if (e == hipSuccess) e = launch_force(c, idx, n_act, acc, pot, stream);
   } else {
@@ -837,6 +838,7 @@ int force_criterion_correct(tsbts_ctx *c, const int32_t *idx, int32_t n_act, dou
   if (n_act <= kSmallAct || share_force(c, n_act).chunk) {
     // small sets: the criterion on the predicted state first, then the force with the
     // corrector (the corrector rewrites the velocities the criterion reads)
+    if (cells_criterion_applies(c, n_act)) (void)cells_prepare(c, stream);
     e = launch_timestep(c, idx, n_act, eta, dtc, stream);
     if (e == hipSuccess) e = launch_force(c, idx, n_act, acc, nullptr, stream, &corr);
   } else {

@@ -45,9 +45,9 @@ hipError_t launch_cell_sort(const CellSort &s, const double *p64, const double *
                             int n_act, hipStream_t st);
 
 // Criterion over the spatial order (timestep_cells.hip): whether it serves a call of
-// n_act targets, its buffers (host set-up; false when they cannot be had, the other
-// kernels then serve the call), and its launch (hipErrorNotReady, with nothing launched,
-// without the buffers).
+// n_act targets; its buffers, host set-up made by every entry point that goes on to
+// launch_timestep with such a call (false when they cannot be had, the other kernels then
+// serve it); and its launch (hipErrorNotReady, with nothing launched, without the buffers).
 bool cells_criterion_applies(const tsbts_ctx *c, int64_t n_act);
 bool cells_prepare(tsbts_ctx *c, hipStream_t st);
 hipError_t launch_timestep_cells(tsbts_ctx *c, const int32_t *idx, int n_act, double eta,

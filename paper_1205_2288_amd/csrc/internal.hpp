@@ -94,8 +94,9 @@ struct tsbts_ctx {
   int64_t split_cap = 0;
   int tune_split = 2;  // 0 off, 1 from kSplitMinAct targets, 2 automatic
   // spatial order of the criterion of large active sets (timestep_cells.hip): one
-  // allocation for npad particles
+  // allocation for npad particles, not tried again once it failed
   void *cell_buf = nullptr;
+  bool cell_refused = false;
   char err[512] = {0};
 };
 

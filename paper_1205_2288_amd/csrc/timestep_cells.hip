@@ -551,11 +551,13 @@ bool cells_criterion_applies(const tsbts_ctx *c, int64_t n_act) {
 
 bool cells_prepare(tsbts_ctx *c, hipStream_t st) {
   if (c->cell_buf) return true;
-  if (!may_allocate(st)) return false;  // the other kernels serve a captured call
+  // the other kernels serve a captured call, and every call once the memory was refused
+  if (c->cell_refused || !may_allocate(st)) return false;
   CellBufs b;
   if (hipMalloc(&c->cell_buf, cell_layout(c, nullptr, &b)) != hipSuccess) {
     (void)hipGetLastError();
     c->cell_buf = nullptr;
+    c->cell_refused = true;
     return false;
   }
   return true;

@@ -71,3 +71,16 @@ def test_call_above_the_benchmark_size(prec, n, k):
     ref = ctx.timestep(idx, 0.1)
     ctx.close()
     assert torch.equal(got, ref) and torch.equal(again, ref)
+
+
+@pytest.mark.parametrize("prec,n,k", [("mixed", 131072, 3500), ("fp64", 131072, 2500)])
+def test_combined_call_as_a_contexts_first(prec, n, k):
+    # nothing else has allocated the form's buffers, and the call takes it all the same
+    ctx = _ctx(n, prec)
+    idx = ctx.idx(np.random.default_rng(n).permutation(n)[:k].astype(np.int32))
+    assert applies(ctx, k)
+    got = ctx.force_criterion(idx, 0.0, 0.1, with_pot=False)[2]
+    again = torch.zeros_like(got)
+    assert launch_cells(ctx, idx, 0.1, again) == 0
+    ctx.close()
+    assert torch.equal(got, again)
