@@ -474,10 +474,9 @@ int tsbts_force_criterion(tsbts_ctx *c, const int32_t *idx, int32_t n_act, doubl
   if (!(eta > 0.0) || !std::isfinite(eta)) return fail(c, TSBTS_EINVAL, "eta must be > 0");
   if (int s = check_pred(c, t_block)) return s;
   hipError_t e;
-  if (n_act <= kSmallAct || share_force(c, n_act).chunk) {
-    // small sets, and sets whose targets the waves share: the criterion and force kernels,
-    // criterion first, on the same predicted state (same definition as the fused pass,
-    // fewer idle lanes)
+  if (criterion_apart(c, n_act)) {
+    // the criterion and force kernels, criterion first, on the same predicted state (same
+    // definition as the fused pass)
     if (int s = ensure_part(c, partial_elems_needed(c, n_act))) return s;
     if (cells_criterion_applies(c, n_act)) (void)cells_prepare(c, stream);
     e = launch_timestep(c, idx, n_act, eta, dtc, stream);
@@ -835,9 +834,9 @@ int force_criterion_correct(tsbts_ctx *c, const int32_t *idx, int32_t n_act, dou
     corr.step = tags->step;
   }
   hipError_t e;
-  if (n_act <= kSmallAct || share_force(c, n_act).chunk) {
-    // small sets: the criterion on the predicted state first, then the force with the
-    // corrector (the corrector rewrites the velocities the criterion reads)
+  if (criterion_apart(c, n_act)) {
+    // the criterion on the predicted state first, then the force with the corrector (the
+    // corrector rewrites the velocities the criterion reads)
     if (cells_criterion_applies(c, n_act)) (void)cells_prepare(c, stream);
     e = launch_timestep(c, idx, n_act, eta, dtc, stream);
     if (e == hipSuccess) e = launch_force(c, idx, n_act, acc, nullptr, stream, &corr);

@@ -845,13 +845,14 @@ ShareShape share_step(const tsbts_ctx *c, int n_act) {
   return share_split(n_act, c->n, 0);
 }
 
-// A bound of the shared-target forms' partials over every active set, which a context
-// reserves so that no later call has to allocate: slices x targets is at most 2048 x 64 +
+// A bound of the shared-target forms' partials (six sums a target in the fused pass) over
+// every active set, which a context reserves so that no later call has to allocate: slices x
+// targets is at most 2048 x 64 +
 // targets (share_split), and a slice holds at least one unit.
 int64_t share_partials_reserve(const tsbts_ctx *c) {
   const int64_t k = std::min<int64_t>(c->n, kShareMaxAct);
   const int64_t units = (c->n + kShare * kChunkTiny - 1) / (kShare * kChunkTiny);
-  return 4 * std::min<int64_t>(2048 * 64 + k, units * k);
+  return 6 * std::min<int64_t>(2048 * 64 + k, units * k);
 }
 
 // The most that a force or criterion call of more than kSmallAct targets needs.  The split,

@@ -8,11 +8,15 @@
 // only through (a_new - a) h / 2 in the active velocities, O(h^2) relative.  In exchange
 // the pair's separation, loads and loop are shared by the two sums.
 //
-// Same scalar-load structure as k_force_scalar (one target per lane, j-particles through
-// wave-uniform loads in units of CH, self / padding masked by a wave vote), with the force
+// Same scalar-load structure as k_force_scalar (one target per lane of the workgroup or, for
+// fewer than kShareMaxAct targets, of every wave; j-particles through wave-uniform loads in
+// units of CH, self / padding masked by a wave vote), in the force's split, with the force
 // and criterion pair arithmetic of the two separate kernels, so that the force is bitwise
-// the one k_force_scalar returns for the same split.  Partials [S][6][n_act]: the force and
-// potential sums, max v^2/r^2 and min s m^(-2/3).
+// the one tsbts_force returns.  Partials [S][6][n_act]: the force and potential sums, max
+// v^2/r^2 and min s m^(-2/3).  Measured (us of device time, a target per lane of the
+// workgroup, of every wave): mixed N = 4096 k = 100 14.2, 13.7, 2000 24.0, 15.1; 131072 100
+// 55.8, 45.9, 777 155, 104; float64 N = 4096 100 16.8, 11.1; 131072 777 224, 162.
+#include "cells.hpp"
 #include "correct.hpp"
 #include "criterion.hpp"
 #include "force_pair.hpp"
@@ -28,7 +32,8 @@ struct FusedArgs {
   const int32_t *idx;
   int n_act;
   SplitPlan plan;
-  int n_units;  // j-units of CH particles
+  int n_units;    // j-units of CH particles, or of kShare * CH (share)
+  int share;      // the waves of a workgroup share 64 targets (ShareShape)
   float eps2f;
   double eps2;
   double eta;
@@ -70,16 +75,18 @@ __device__ __forceinline__ void fused_unit(const FusedArgs &A, const typename V:
   }
 }
 
-template <class V, int NEWTON, int POT, int CH>
+template <class V, int NEWTON, int POT, int CH, int SH>
 __global__ __launch_bounds__(kWG) void k_fused(FusedArgs A) {
   using F = typename V::F;
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  const int w = SH == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int itile, slice;
   split_tile(blockIdx.x, A.plan, itile, slice);
   if (slice >= A.plan.n_slices) return;
   const int jt0 = slice * A.plan.tiles_per_slice;
   const int jt1 = min(jt0 + A.plan.tiles_per_slice, A.n_units);
   const F eps2 = sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2);
-  const int q = itile * kWG + static_cast<int>(threadIdx.x);
+  const int q = SH == 1 ? itile * kWG + static_cast<int>(threadIdx.x) : itile * 64 + lane;
   const int g = A.idx[min(q, A.n_act - 1)];
   const typename V::I If = V::load_i(A.p32, A.p64, A.npad, g);
   const typename StepRec<V>::I Ic = load_iv<V>(A, g);
@@ -87,7 +94,8 @@ __global__ __launch_bounds__(kWG) void k_fused(FusedArgs A) {
   F qm = F(0);
   F sm = sizeof(F) == 4 ? static_cast<F>(__builtin_inff()) : static_cast<F>(__builtin_inf());
   for (int jt = jt0; jt < jt1; ++jt) {
-    const int64_t jbase = static_cast<int64_t>(jt) * CH;
+    const int64_t jbase = (static_cast<int64_t>(jt) * SH + w) * CH;
+    if (SH > 1 && jbase >= A.npad) break;
     F fx = F(0), fy = F(0), fz = F(0), fp = F(0);
     if (__ballot(g >= jbase && g < jbase + CH) != 0 || jbase + CH > A.n)
       fused_unit<V, NEWTON, 1, POT, CH>(A, If, Ic, g, jbase, eps2, fx, fy, fz, fp, qm, sm);
@@ -98,8 +106,34 @@ __global__ __launch_bounds__(kWG) void k_fused(FusedArgs A) {
     sz += static_cast<double>(fz);
     sp += static_cast<double>(fp);
   }
-  if (q >= A.n_act) return;
   double *out = A.part + static_cast<int64_t>(slice) * 6 * A.n_act;
+  if constexpr (SH > 1) {
+    // wave c: sum c of the waves, in wave order; wave 0 the maxima too, wave 1 the minima
+    static_assert(SH == 4, "a wave per sum");
+    __shared__ double red[SH][6][64];
+    red[w][0][lane] = sx;
+    red[w][1][lane] = sy;
+    red[w][2][lane] = sz;
+    red[w][3][lane] = sp;
+    red[w][4][lane] = static_cast<double>(qm);
+    red[w][5][lane] = static_cast<double>(sm);
+    __syncthreads();
+    if (q >= A.n_act) return;
+    double x = red[0][w][lane];
+#pragma unroll
+    for (int u = 1; u < SH; ++u) x += red[u][w][lane];
+    out[w * static_cast<int64_t>(A.n_act) + q] = x;
+    if (w >= 2) return;
+    double y = red[0][4 + w][lane];
+#pragma unroll
+    for (int u = 1; u < SH; ++u) {
+      const double z = red[u][4 + w][lane];
+      y = w == 0 ? fmax(y, z) : fmin(y, z);
+    }
+    out[(4 + w) * static_cast<int64_t>(A.n_act) + q] = y;
+    return;
+  }
+  if (q >= A.n_act) return;
   out[q] = sx;
   out[A.n_act + q] = sy;
   out[2 * A.n_act + q] = sz;
@@ -193,22 +227,29 @@ __global__ __launch_bounds__(64 * kRowsWaves) void k_fused_reduce_rows(FusedArgs
   }
 }
 
-template <class V, int NEWTON, int CH>
+template <class V, int NEWTON, int CH, int SH>
 void launch_main(FusedArgs &A, hipStream_t st) {
   const dim3 grid(A.plan.nblk), block(kWG);
   if (A.pot)
-    hipLaunchKernelGGL((k_fused<V, NEWTON, 1, CH>), grid, block, 0, st, A);
+    hipLaunchKernelGGL((k_fused<V, NEWTON, 1, CH, SH>), grid, block, 0, st, A);
   else
-    hipLaunchKernelGGL((k_fused<V, NEWTON, 0, CH>), grid, block, 0, st, A);
+    hipLaunchKernelGGL((k_fused<V, NEWTON, 0, CH, SH>), grid, block, 0, st, A);
 }
 
 template <class V, int NEWTON>
 hipError_t run(FusedArgs &A, int chunk, hipStream_t st) {
-  if (chunk == kChunkSmall)
-    launch_main<V, NEWTON, kChunkSmall>(A, st);
+  if (A.share && chunk == kChunkTiny)
+    launch_main<V, NEWTON, kChunkTiny, kShare>(A, st);
+  else if (A.share && chunk == kChunkSmall)
+    launch_main<V, NEWTON, kChunkSmall, kShare>(A, st);
+  else if (A.share)
+    launch_main<V, NEWTON, kTJ, kShare>(A, st);
+  else if (chunk == kChunkSmall)
+    launch_main<V, NEWTON, kChunkSmall, 1>(A, st);
   else
-    launch_main<V, NEWTON, kTJ>(A, st);
-  if (use_rows_reduce(A.plan.n_slices, A.n_act)) {
+    launch_main<V, NEWTON, kTJ, 1>(A, st);
+  // the force's choice for the same call
+  if (force_rows_reduce(A.plan.n_slices, A.n_act, A.share != 0)) {
     const int nb = (A.n_act + 63) / 64;
     hipLaunchKernelGGL((k_fused_reduce_rows<V, NEWTON>), dim3(nb), dim3(64 * kRowsWaves), 0, st,
                        A);
@@ -222,12 +263,37 @@ hipError_t run(FusedArgs &A, int chunk, hipStream_t st) {
   return hipGetLastError();
 }
 
+// The force's split of the same call.
+SplitPlan fused_plan(const tsbts_ctx *c, int n_act, int *chunk, int *n_units, int *share) {
+  const ShareShape sh = share_force(c, n_act);
+  *share = sh.chunk != 0;
+  *chunk = sh.chunk ? sh.chunk : scalar_chunk(c, n_act, 1);
+  *n_units = sh.chunk ? sh.n_units : static_cast<int>(c->npad / *chunk);
+  return sh.chunk ? sh.plan : plan_split(n_act, 1, *n_units, c->tune_blocks);
+}
+
 }  // namespace
 
+// Small sets, whose lanes the fused pass would leave idle, and sets whose criterion over the
+// spatial order saves more than the fused pass does.  Measured (us of device time, fused /
+// apart): mixed N = 131072 k = 2500 282 / 302, 3000 321 / 323, 3500 364 / 342; 262144 2000 435 /
+// 455, 2500 550 / 525; float64 32768 3500 159 / 163, 4095 178 / 170; 65536 2000 184 / 200, 2500
+// 239 / 233; 131072 1500 288 / 305, 2000 351 / 320; 262144 1100 435 / 468, 1500 580 / 511.  In
+// mixed precision few targets of very many particles also go apart: 64 of N = 131072 45.8 /
+// 44.8, of 262144 76 / 68, 180 91 / 90.  Sets of 4096 targets or more stay in one pass.
+bool criterion_apart(const tsbts_ctx *c, int n_act) {
+  if (n_act <= kSmallAct) return true;
+  if (!share_force(c, n_act).chunk) return false;
+  const bool fp64 = c->precision == TSBTS_FP64;
+  if (!fp64 && c->n >= 196608 && n_act <= 128) return true;
+  return cells_criterion_applies(c, n_act) &&
+         (fp64 ? c->n * (n_act - 900) >= 95000000 : c->n * (n_act - 1300) >= 260000000);
+}
+
 int64_t fused_partials_needed(const tsbts_ctx *c, int n_act) {
-  const SplitPlan p =
-      plan_split(n_act, 1, c->npad / scalar_chunk(c, n_act, 1), c->tune_blocks);
-  return static_cast<int64_t>(p.n_slices) * 6 * n_act;
+  int chunk, n_units, share;
+  return static_cast<int64_t>(fused_plan(c, n_act, &chunk, &n_units, &share).n_slices) * 6 *
+         n_act;
 }
 
 hipError_t launch_fused(tsbts_ctx *c, const int32_t *idx, int n_act, double eta, double *acc,
@@ -240,9 +306,8 @@ hipError_t launch_fused(tsbts_ctx *c, const int32_t *idx, int n_act, double eta,
   A.v64 = c->v64;
   A.idx = idx;
   A.n_act = n_act;
-  const int chunk = scalar_chunk(c, n_act, 1);
-  A.n_units = static_cast<int>(c->npad / chunk);
-  A.plan = plan_split(n_act, 1, A.n_units, c->tune_blocks);
+  int chunk;
+  A.plan = fused_plan(c, n_act, &chunk, &A.n_units, &A.share);
   A.eps2f = static_cast<float>(c->eps * c->eps);
   A.eps2 = c->eps * c->eps;
   A.eta = eta;

@@ -328,7 +328,7 @@ __host__ __device__ inline bool use_wave_reduce(int n_slices, int64_t n_targets)
 // slices, 30.7 -> 27.8 us a call; 500 of N = 4096, 64 slices, 9.6 -> 10.4) and kRowsFewStep
 // of the criterion (1500 28.4 -> 25.5, 500 12.5 -> 11.9), there from kRowsTinyStep where
 // there are kRowsTinySlices at most (16 of N = 20011, 79 slices, 8.1 -> 7.9; of N = 32768,
-// 128 slices, 8.1 -> 8.6).  Few targets are one such workgroup, whose waves would walk all
+// 128 slices, 8.1 -> 8.6)).  Few targets are one such workgroup, whose waves would walk all
 // slices: one target's force at N = 60000, 235 slices, 5.1 us with a wave per target, 11.0
 // with rows.
 constexpr int64_t kRowsReduceMinTargets = 2048;
@@ -625,6 +625,9 @@ hipError_t launch_force_predicted(tsbts_ctx *c, const int32_t *idx, int n_act, d
 // Whether launch_force_predicted takes the criterion of n_act targets itself: launches of
 // one workgroup.
 bool small_criterion_fused(const tsbts_ctx *c, int n_act);
+// Whether a combined force + criterion call runs the criterion's and the force's own kernels
+// instead of the fused pass (fused.hip).
+bool criterion_apart(const tsbts_ctx *c, int n_act);
 // Symmetric all-targets criterion (timestep_sym.hip); plan from sym_plan.  With `set`, the
 // kernels run on that particle set instead of the context's predicted arrays; with `raw`,
 // each target's maximum and minimum go there unfinished ([2][n_act]) instead of to dtc.

@@ -36,7 +36,10 @@ int route_share_tiles() { return kShareTiles; }
 }
 
 extern "C" {
-int64_t route_partials(const tsbts_ctx *c, int k) { return partial_elems_needed(c, k); }
+int64_t route_partials(const tsbts_ctx *c, int k) {
+  const bool fused = k > kSmallAct && k < kShareMaxAct;
+  return std::max(partial_elems_needed(c, k), fused ? fused_partials_needed(c, k) : 0);
+}
 int64_t route_reserve(const tsbts_ctx *c) {
   return std::max(gather_partials_reserve(c), share_partials_reserve(c));
 }
@@ -53,4 +56,8 @@ int route_step_rows(int slices, int64_t targets, int shared) {
 
 extern "C" int route_cells(const tsbts_ctx *c, int64_t k) {
   return cells_criterion_applies(c, k) ? 1 : 0;
+}
+
+extern "C" {
+int route_apart(const tsbts_ctx *c, int k) { return criterion_apart(c, k) ? 1 : 0; }
 }

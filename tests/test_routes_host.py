@@ -34,7 +34,7 @@ def routes(tmp_path_factory):
     for name in ("route_reserve", "route_partials"):
         getattr(r, name).restype = ctypes.c_int64
     r.route_cells.argtypes = [ctypes.c_void_p, ctypes.c_int64]
-    for name in ("route_force_done", "route_share_done", "route_partials"):
+    for name in ("route_force_done", "route_share_done", "route_partials", "route_apart"):
         getattr(r, name).argtypes = [ctypes.c_void_p, ctypes.c_int]
     return r
 
@@ -116,3 +116,23 @@ def test_spatial_order_serves_where_it_is_faster(routes, make, precision):
         assert not routes.route_cells(make(n, precision), k), (n, k)
     for n, k in ORDER[precision]:
         assert routes.route_cells(make(n, precision), k), (n, k)
+
+
+# (particles, targets) at which the fused pass takes less than 0.97 of the time of the two
+# separate kernels, and at which it takes more than 1.03 of it
+FUSED = {MIXED: [(512, 33), (4096, 100), (4096, 3000), (8192, 300), (16384, 1100), (32768, 4095),
+                 (65536, 64), (65536, 2000), (65536, 4095), (131072, 256), (131072, 2500),
+                 (262144, 500), (262144, 2000)],
+         FP64: [(512, 33), (4096, 300), (8192, 500), (16384, 3500), (32768, 2500), (65536, 2000),
+                (131072, 1500), (262144, 1100)]}
+APART = {MIXED: [(300, 20), (131072, 3500), (262144, 33), (262144, 100), (262144, 2500)],
+         FP64: [(300, 20), (32768, 4095), (65536, 2500), (131072, 2000), (262144, 1500)]}
+
+
+@pytest.mark.parametrize("precision", [FP64, MIXED])
+def test_combined_calls_take_the_faster_form(routes, make, precision):
+    for n, k in FUSED[precision]:
+        assert not routes.route_apart(make(n, precision), k), (n, k)
+    for n, k in APART[precision]:
+        assert routes.route_apart(make(n, precision), k), (n, k)
+    assert not routes.route_apart(make(131072, precision), 4096)
