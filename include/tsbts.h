@@ -78,7 +78,10 @@ int tsbts_destroy(tsbts_ctx *ctx);
 #define TSBTS_TUNE_SPLIT 6
 
 /* Launch-shape tuning of the pair kernels (force, criterion, adjoint); host-side only.
- *   TSBTS_TUNE_BLOCKS: workgroups a split-j launch aims for (64 .. 65536; default 8192)
+ *   TSBTS_TUNE_BLOCKS: workgroups a split-j launch aims for (64 .. 65536; default 8192;
+ *                      another count keeps the kernels that split by it, as a set kernel
+ *                      form or unit does: not those whose waves share targets, nor the
+ *                      criterion's spatial order)
  *   TSBTS_TUNE_IPL:    kernel form of the force and criterion (0 = automatic: the force,
  *                      and the criterion of few targets or many, read the j-particles
  *                      through wave-uniform scalar loads, sets below 4096 targets with

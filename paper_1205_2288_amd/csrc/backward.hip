@@ -685,8 +685,7 @@ SplitPlan plan_all(const BwdArgs &A) { return plan_split(A.npad, 1, A.npad / kTJ
 // 46.0; 1024 of 16384 57.5, 50.7; 4096 of 16384 107, 107; 8192 of 131072 1200, 1225.
 constexpr int64_t kShareBwdPairs = int64_t(1) << 25;
 bool share_bwd(const tsbts_ctx *c, int64_t n_act) {
-  return c->precision == TSBTS_FP64 && force_scalar_j(c) && c->tune_chunk == 0 &&
-         c->n * n_act < kShareBwdPairs;
+  return c->precision == TSBTS_FP64 && automatic_form(c) && c->n * n_act < kShareBwdPairs;
 }
 
 // Rows up to which k_bwd_reduce_rows also serves few slices (a thread per row is too few).

@@ -827,7 +827,7 @@ ShareShape share_split(int64_t n_targets, int64_t n_cols, int chunk) {
 namespace {
 
 bool share_applies(const tsbts_ctx *c, int n_act) {
-  return force_scalar_j(c) && c->tune_chunk == 0 && n_act < kShareMaxAct;
+  return automatic_form(c) && n_act < kShareMaxAct;
 }
 
 }  // namespace

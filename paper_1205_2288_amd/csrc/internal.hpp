@@ -23,6 +23,7 @@ enum { P64_X = 0, P64_M = 3, P64_W = 4, P64_PLANES = 5 };
 enum { P32_XH = 0, P32_M = 3, P32_XL = 4, P32_W = 7, P32_VX = 8, P32_E = 11, P32_PLANES = 12 };
 // History record state planes: r(3), v(3), a(3)
 constexpr int kHistPlanes = 9;
+constexpr int kDefaultBlocks = 8192;  // workgroups a split-j launch aims for
 
 struct History {
   // records being appended during a pass
@@ -68,7 +69,7 @@ struct tsbts_ctx {
   // native host scheduler (tsbts_sched_*), owned
   void *sched = nullptr;
   // launch-shape tuning (tsbts_tune)
-  int tune_blocks = 8192;
+  int tune_blocks = tsbts::kDefaultBlocks;
   int tune_ipl = 0;
   int tune_chunk = 0;  // j-particles per split unit of the scalar-load kernels (0: automatic)
   int tune_sym = 2;    // symmetric all-targets kernels: 0 off, 1 on, 2 automatic
@@ -413,6 +414,11 @@ inline int targets_per_lane(const tsbts_ctx *c, int n_act) {
 // The force kernel reads its j-particles through wave-uniform (scalar) loads unless a
 // targets-per-lane count was set, which selects the LDS-staged kernel.
 inline bool force_scalar_j(const tsbts_ctx *c) { return c->tune_ipl == 0; }
+// The automatic kernel form: a workgroup count, targets per lane or unit that was set keeps
+// the forms it is defined for.
+inline bool automatic_form(const tsbts_ctx *c) {
+  return force_scalar_j(c) && c->tune_chunk == 0 && c->tune_blocks == kDefaultBlocks;
+}
 inline int force_targets_per_lane(const tsbts_ctx *c, int n_act) {
   return force_scalar_j(c) ? 1 : targets_per_lane(c, n_act);
 }

@@ -523,8 +523,7 @@ hipError_t run(const tsbts_ctx *c, const CellBufs &b, const int32_t *idx, int n_
 
 bool cells_criterion_applies(const tsbts_ctx *c, int64_t n_act) {
   // a call tuned to a kernel form keeps it
-  if (c->tune_sym != 2 || c->tune_split != 2 || !force_scalar_j(c) || c->tune_chunk != 0)
-    return false;
+  if (c->tune_sym != 2 || c->tune_split != 2 || !automatic_form(c)) return false;
   // The order and the tests take as long as kPairs pairs and kTargets targets of the gather
   // kernels (half as many in float64 from kShareMaxAct targets).  Measured either side of
   // the line (us, this / gather): mixed N = 16384 k = 7061 72 / 71, 7300 70 / 78; 32768 4023

@@ -61,3 +61,10 @@ extern "C" int route_cells(const tsbts_ctx *c, int64_t k) {
 extern "C" {
 int route_apart(const tsbts_ctx *c, int k) { return criterion_apart(c, k) ? 1 : 0; }
 }
+
+extern "C" {
+void route_tune_blocks(tsbts_ctx *c, int blocks) { c->tune_blocks = blocks; }
+int route_share(const tsbts_ctx *c, int k) {
+  return (share_force(c, k).chunk != 0) + 2 * (share_step(c, k).chunk != 0);
+}
+}

@@ -34,7 +34,8 @@ def routes(tmp_path_factory):
     for name in ("route_reserve", "route_partials"):
         getattr(r, name).restype = ctypes.c_int64
     r.route_cells.argtypes = [ctypes.c_void_p, ctypes.c_int64]
-    for name in ("route_force_done", "route_share_done", "route_partials", "route_apart"):
+    for name in ("route_force_done", "route_share_done", "route_partials", "route_apart", "route_share",
+                 "route_tune_blocks"):
         getattr(r, name).argtypes = [ctypes.c_void_p, ctypes.c_int]
     return r
 
@@ -136,3 +137,17 @@ def test_combined_calls_take_the_faster_form(routes, make, precision):
     for n, k in APART[precision]:
         assert routes.route_apart(make(n, precision), k), (n, k)
     assert not routes.route_apart(make(131072, precision), 4096)
+
+
+@pytest.mark.parametrize("precision", [FP64, MIXED])
+def test_tuned_workgroup_count_keeps_its_forms(routes, make, precision):
+    # the shared-target kernels and the spatial order have splits of their own, so a call
+    # tuned to a workgroup count does not take them
+    c = make(131072, precision)
+    assert routes.route_share(c, 200) == 3 and routes.route_cells(c, 40000)
+    default = routes.route_partials(c, 2000)
+    routes.route_tune_blocks(c, 64)
+    assert routes.route_share(c, 200) == 0 and not routes.route_cells(c, 40000)
+    assert routes.route_partials(c, 2000) < default
+    routes.route_tune_blocks(c, 8192)
+    assert routes.route_share(c, 200) == 3 and routes.route_cells(c, 40000)
