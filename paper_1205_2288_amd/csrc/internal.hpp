@@ -134,7 +134,9 @@ __device__ __forceinline__ double rsqrt_f64(double s) {
   return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
-// k s^(-3/2) likewise: k y^3 (1 + 3 e/2 + 15 e^2/8).  With POT also adds k s^(-1/2) to pot.
+// k s^(-3/2) likewise: k y^3 (1 + 3 e/2 + 15 e^2/8).  With POT also adds k s^(-1/2) to pot,
+// in three operations, the last one the sum's (float64 with the potential, all of N = 32767:
+// 738 -> 704 us, 16384 of 131072 1451 -> 1389; two Newton steps took 724 and 1426).
 template <int POT>
 __device__ __forceinline__ double scaled_inv_cube_f64(double s, double k, double &pot) {
   const double y = rsq_f64_approx(s);
@@ -142,7 +144,7 @@ __device__ __forceinline__ double scaled_inv_cube_f64(double s, double k, double
   const double e = fma(-s, t, 1.0);
   const double ky = k * y;
   const double a = ky * t;
-  if (POT) pot += fma(ky * e, fma(0.375, e, 0.5), ky);
+  if (POT) pot = fma(ky, fma(e, fma(0.375, e, 0.5), 1.0), pot);
   return fma(a * e, fma(1.875, e, 1.5), a);
 }
 

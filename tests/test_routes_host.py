@@ -2,6 +2,7 @@
 call takes, through tests/host/routes.cpp."""
 import ctypes
 import os
+import re
 import subprocess
 
 import pytest
@@ -151,3 +152,23 @@ def test_tuned_workgroup_count_keeps_its_forms(routes, make, precision):
     assert routes.route_partials(c, 2000) < default
     routes.route_tune_blocks(c, 8192)
     assert routes.route_share(c, 200) == 3 and routes.route_cells(c, 40000)
+
+
+def test_float64_potential_costs_three_operations(tmp_path):
+    # the potential's share of a float64 pair, counted in the kernels' own assembly
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    out = str(tmp_path / "ops.s")
+    res = subprocess.run([HIPCC, "--offload-device-only", "--offload-arch=gfx950", "-O3",
+                          "-std=c++17", "-Xclang", "-target-feature", "-Xclang",
+                          "-packed-fp32-ops", "-S", "-I", os.path.join(PKG, "csrc"),
+                          os.path.join(ROOT, "tests", "host", "ops.hip"), "-o", out],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-3000:]
+    text = open(out).read()
+    ops = {}
+    for name in ("k_force_only", "k_with_potential"):
+        body = text.split(f"\n{name}:")[1].split("s_endpgm")[0]
+        ops[name] = len(re.findall(r"\bv_(?:fma|fmac|mul|add)_f64", body))
+    assert ops["k_force_only"] >= 6
+    assert ops["k_with_potential"] - ops["k_force_only"] == 3
