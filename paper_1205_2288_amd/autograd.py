@@ -62,16 +62,20 @@ def tsbts_force(r, m, idx, ctx: Context):
 
 
 class _State:
-    """r, v, a [3, n], t_last and dt [n] of a run as views of one buffer, `flat`: a
-    checkpoint, a copy back or a step's pre-step state is one copy of 11 n values (five
-    copies took 5 launches, which set the time of a run on few particles: 52 of the 131
-    launches of four block steps and their gradient were copies)."""
+    """r, v, a [3, n], t_last and dt [n] of a run.  Those that its checkpoints hold are
+    views of one buffer, `flat`: a checkpoint, a copy back or a step's pre-step state is one
+    copy (five copies took 5 launches, which set the time of a run on few particles: 52 of
+    the 131 launches of four block steps and their gradient were copies).  `flat` holds
+    9 n values, r, v and a, when t_last is given, 10 n with t_last when dt is given, else
+    11 n; arrays given are the run's own and are not saved."""
 
-    def __init__(self, ctx: Context, flat):
+    def __init__(self, ctx: Context, flat, t_last=None, dt=None):
         n = ctx.n
         self.flat = flat
         self.r, self.v, self.a = (flat[3 * n * c:3 * n * (c + 1)].view(3, n) for c in range(3))
-        self.t_last, self.dt = flat[9 * n:10 * n], flat[10 * n:]
+        self.kept = 3 if t_last is not None else 4 if dt is not None else 5
+        self.t_last = flat[9 * n:10 * n] if t_last is None else t_last
+        self.dt = flat[10 * n:] if dt is None else dt
 
     def _arrays(self):
         return self.r, self.v, self.a, self.t_last, self.dt
@@ -88,34 +92,42 @@ class _State:
     def save(self):
         if self.whole:
             return self.flat.clone()
-        return torch.cat([x.reshape(-1) for x in self._arrays()])
+        return torch.cat([x.reshape(-1) for x in self._arrays()[:self.kept]])
 
     def restore(self, flat):
         if self.whole:
             self.flat.copy_(flat)
             return
         done = 0
-        for x in self._arrays():
+        for x in self._arrays()[:self.kept]:
             x.copy_(flat[done:done + x.numel()].view(x.shape))
             done += x.numel()
 
     @classmethod
-    def start(cls, ctx: Context, r0, v0, m, dt):
-        """r0, v0 at time 0 with steps dt; zero accelerations, which the prediction at time 0
-        reads before the first force gives them."""
-        st = cls(ctx, torch.zeros(11 * ctx.n, dtype=torch.float64, device=ctx.device))
-        st.r.copy_(r0.reshape(3, ctx.n))
-        st.v.copy_(v0.reshape(3, ctx.n))
-        if isinstance(dt, float):
-            st.dt.fill_(dt)
-        else:
-            st.dt.copy_(dt.reshape(ctx.n))
+    def start(cls, ctx: Context, r0, v0, m, dt, kept=5):
+        """r0, v0 at time 0 with steps dt, checkpoints of the first `kept` arrays; zero
+        accelerations, which the prediction at time 0 reads before the first force gives
+        them."""
+        n, like = ctx.n, dict(dtype=torch.float64, device=ctx.device)
+        own = None  # the steps, where the checkpoints leave them out
+        if kept < 5:
+            own = torch.full((n,), dt, **like) if isinstance(dt, float) else dt.to(**like)
+        zero = torch.zeros((11 if own is None else 10) * n, **like)
+        st = cls(ctx, zero[:(6 + kept) * n], zero[9 * n:10 * n] if kept < 4 else None, own)
+        if own is None:
+            st.dt.copy_(dt.reshape(n))
+        st.r.copy_(r0.reshape(3, n))
+        st.v.copy_(v0.reshape(3, n))
         return st.bind(ctx, m.clone())
 
     @classmethod
-    def like(cls, ctx: Context, flat, m):
+    def like(cls, ctx: Context, flat, m, t_last=None, dt=None):
         """A bound state of its own (its values come from a later restore)."""
-        return cls(ctx, torch.empty_like(flat)).bind(ctx, m)
+        return cls(ctx, torch.empty_like(flat), t_last, dt).bind(ctx, m)
+
+
+def _positions(ctx: Context, flat):
+    return flat[:3 * ctx.n].view(3, ctx.n)
 
 
 class TsbtsLeapfrog(torch.autograd.Function):
@@ -126,7 +138,7 @@ class TsbtsLeapfrog(torch.autograd.Function):
         n = ctx.n
         dev = ctx.device
         r0, v0, m = (x.detach().contiguous() for x in (r0, v0, m))
-        st = _State.start(ctx, r0, v0, m, float(h))
+        st = _State.start(ctx, r0, v0, m, float(h), kept=3)
         every = ctx.idx(torch.arange(n, dtype=torch.int32))
         acc = torch.empty((3, n), dtype=torch.float64, device=dev)
         ctx.predict(0.0)
@@ -138,6 +150,7 @@ class TsbtsLeapfrog(torch.autograd.Function):
             _step(ctx, every, acc, s, h)
         fctx.tsbts = ctx
         fctx.meta = (h, steps, era)
+        fctx.dt = st.dt
         fctx.checkpoints = checkpoints
         fctx.save_for_backward(m)
         fctx.every = every
@@ -158,12 +171,13 @@ class TsbtsLeapfrog(torch.autograd.Function):
         g = z()
         mbar = torch.zeros(n, dtype=torch.float64, device=dev)
         acc = torch.empty((3, n), dtype=torch.float64, device=dev)
-        st = _State.like(ctx, fctx.checkpoints[0][1], m)
+        st = _State.like(ctx, fctx.checkpoints[0][1], m, torch.empty_like(mbar), fctx.dt)
         for (s0, flat) in reversed(fctx.checkpoints):
             s1 = min(s0 + era, steps)
             # recompute the era from its checkpoint, keeping the positions of every step;
             # the last step's are its prediction, its force is not needed
             st.restore(flat)
+            st.t_last.fill_(s0 * h)
             pos = []
             for s in range(s0, s1 - 1):
                 _step(ctx, every, acc, s, h)
@@ -177,7 +191,7 @@ class TsbtsLeapfrog(torch.autograd.Function):
                     ctx.load_positions(pos[s - s0], m, tb)
                 ctx.force_backward(every, tb, g, None, rbar, mbar)   # through a_{s+1}
                 ctx.leapfrog_adjoint(1, h, rbar, vbar, abar, g)      # adjoints of step s
-        ctx.load_positions(_State(ctx, fctx.checkpoints[0][1]).r, m, 0.0)
+        ctx.load_positions(_positions(ctx, fctx.checkpoints[0][1]), m, 0.0)
         ctx.force_backward(every, 0.0, abar, None, rbar, mbar)      # through a_0
         return rbar, vbar, mbar, None, None, None, None
 
@@ -246,7 +260,7 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
         dev = ctx.device
         sched = BlockSchedule(ctx, dt, t_end)
         r0, v0, m = (x.detach().contiguous() for x in (r0, v0, m))
-        st = _State.start(ctx, r0, v0, m, torch.tensor(sched.dt))
+        st = _State.start(ctx, r0, v0, m, torch.tensor(sched.dt), kept=4)
         every = sched.sets[-1]
         buf = torch.empty(3 * n, dtype=torch.float64, device=dev)
         ctx.predict(0.0)
@@ -259,6 +273,7 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
         fctx.tsbts = ctx
         fctx.sched = sched
         fctx.era = era
+        fctx.dt = st.dt
         fctx.checkpoints = checkpoints
         fctx.every = every
         fctx.save_for_backward(m)
@@ -279,7 +294,7 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
         buf = torch.empty(3 * n, dtype=torch.float64, device=dev)
         seeds = torch.empty(3 * n, dtype=torch.float64, device=dev)
         first = fctx.checkpoints[0][1]
-        st = _State.like(ctx, first, m)
+        st = _State.like(ctx, first, m, dt=fctx.dt)
         for (s0, flat) in reversed(fctx.checkpoints):
             s1 = min(s0 + era, sched.K)
             st.restore(flat)
@@ -301,7 +316,7 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
                 ctx.block_adjoint(0, idx, tb, rbar, vbar, abar, pbar, sd)
                 ctx.force_backward(idx, tb, sd, None, pbar, mbar)
                 ctx.block_adjoint(1, None, tb, rbar, vbar, abar, pbar, None)
-        ctx.load_positions(_State(ctx, first).r, m, 0.0)
+        ctx.load_positions(_positions(ctx, first), m, 0.0)
         ctx.force_backward(fctx.every, 0.0, abar, None, rbar, mbar)   # through a_0
         return rbar, vbar, mbar, None, None, None, None
 
@@ -496,7 +511,7 @@ class TsbtsScheduleLeapfrog(torch.autograd.Function):
             rbar, vbar, abar = acc_r, acc_v, acc_a
             st.restore(start)
         ctx.history_clear()
-        ctx.load_positions(_State(ctx, first).r, m, 0.0)
+        ctx.load_positions(_positions(ctx, first), m, 0.0)
         ctx.force_backward(fctx.every, 0.0, abar, None, rbar, mbar)   # through a_0
         return rbar, vbar, mbar, None, None
 
