@@ -834,7 +834,7 @@ int force_criterion_correct(tsbts_ctx *c, const int32_t *idx, int32_t n_act, dou
     corr.step = tags->step;
   }
   hipError_t e;
-  if (criterion_apart(c, n_act)) {
+  if (criterion_first(c, n_act)) {
     // the criterion on the predicted state first, then the force with the corrector (the
     // corrector rewrites the velocities the criterion reads)
     if (cells_criterion_applies(c, n_act)) (void)cells_prepare(c, stream);

@@ -636,6 +636,8 @@ bool small_criterion_fused(const tsbts_ctx *c, int n_act);
 // Whether a combined force + criterion call runs the criterion's and the force's own kernels
 // instead of the fused pass (fused.hip).
 bool criterion_apart(const tsbts_ctx *c, int n_act);
+// The same for the native scheduler's step, whose host waits for the criterion alone.
+bool criterion_first(const tsbts_ctx *c, int n_act);
 // Symmetric all-targets criterion (timestep_sym.hip); plan from sym_plan.  With `set`, the
 // kernels run on that particle set instead of the context's predicted arrays; with `raw`,
 // each target's maximum and minimum go there unfinished ([2][n_act]) instead of to dtc.

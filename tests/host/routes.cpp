@@ -68,3 +68,5 @@ int route_share(const tsbts_ctx *c, int k) {
   return (share_force(c, k).chunk != 0) + 2 * (share_step(c, k).chunk != 0);
 }
 }
+
+extern "C" int route_first(const tsbts_ctx *c, int k) { return criterion_first(c, k) ? 1 : 0; }

@@ -35,7 +35,7 @@ def routes(tmp_path_factory):
     for name in ("route_reserve", "route_partials"):
         getattr(r, name).restype = ctypes.c_int64
     r.route_cells.argtypes = [ctypes.c_void_p, ctypes.c_int64]
-    for name in ("route_force_done", "route_share_done", "route_partials", "route_apart", "route_share",
+    for name in ("route_force_done", "route_share_done", "route_partials", "route_apart", "route_share", "route_first",
                  "route_tune_blocks"):
         getattr(r, name).argtypes = [ctypes.c_void_p, ctypes.c_int]
     return r
@@ -172,3 +172,13 @@ def test_float64_potential_costs_three_operations(tmp_path):
         ops[name] = len(re.findall(r"\bv_(?:fma|fmac|mul|add)_f64", body))
     assert ops["k_force_only"] >= 6
     assert ops["k_with_potential"] - ops["k_force_only"] == 3
+
+
+@pytest.mark.parametrize("precision", [FP64, MIXED])
+@pytest.mark.parametrize("n", [64, 1000, 131072])
+def test_native_step_takes_the_criterion_before_the_force(routes, make, precision, n):
+    # the host goes on as soon as it has the criterion, so the step never waits for a fused
+    # pass below 4096 targets
+    c = make(n, precision)
+    assert all(routes.route_first(c, k) for k in (1, 32, 33, 300, 4095) if k <= n)
+    assert not routes.route_first(c, 4096)
