@@ -92,19 +92,20 @@ __global__ __launch_bounds__(kWG) void k_energy_pairs(EnergyArgs A) {
     tile_pair(b >> A.part_bits, A.T, I, J);
     const int part = static_cast<int>(b) & ((1 << A.part_bits) - 1);
     const int64_t i = I * kTE + tid;
-    // targets past the last particle read its position and count for nothing
+    // targets past the last particle read its position and count for nothing: they lie in
+    // the last tile row, whose one pair is diagonal and leaves out every j <= i, and have no
+    // mass and no kinetic energy
     const int64_t ii = i < n ? i : n - 1;
     const double xi = A.r[ii], yi = A.r[n + ii], zi = A.r[2 * n + ii];
     const double mi = i < n ? A.m[ii] : 0.0;
-    if (I == J && part == 0) {
-      const double vx = A.v[ii], vy = A.v[n + ii], vz = A.v[2 * n + ii];
+    if (I == J && part == 0 && i < n) {
+      const double vx = A.v[i], vy = A.v[n + i], vz = A.v[2 * n + i];
       pk += 0.5 * mi * (vx * vx + vy * vy + vz * vz);
     }
     const int64_t j0 = J * kTE + part * len, j1 = j0 + len < n ? j0 + len : n;
     const double w = I != J ? energy_tile<0>(A, j0, j1, i, xi, yi, zi)
                             : energy_tile<1>(A, j0, j1, i, xi, yi, zi);
-    // (a target past the last particle may have met itself at no distance)
-    if (i < n) pw = fma(mi, 0.5 * w, pw);
+    pw = fma(mi, 0.5 * w, pw);
   }
   pw = wave_sum(pw);
   pk = wave_sum(pk);
