@@ -66,16 +66,15 @@ class _State:
     views of one buffer, `flat`: a checkpoint, a copy back or a step's pre-step state is one
     copy (five copies took 5 launches, which set the time of a run on few particles: 52 of
     the 131 launches of four block steps and their gradient were copies).  `flat` holds
-    9 n values, r, v and a, when t_last is given, 10 n with t_last when dt is given, else
-    11 n; arrays given are the run's own and are not saved."""
+    11 n values, or all but the steps, 10 n, where those are given: they are the run's own
+    then and are not saved."""
 
-    def __init__(self, ctx: Context, flat, t_last=None, dt=None):
+    def __init__(self, ctx: Context, flat, dt=None):
         n = ctx.n
         self.flat = flat
         self.r, self.v, self.a = (flat[3 * n * c:3 * n * (c + 1)].view(3, n) for c in range(3))
-        self.kept = 3 if t_last is not None else 4 if dt is not None else 5
-        self.t_last = flat[9 * n:10 * n] if t_last is None else t_last
-        self.dt = flat[10 * n:] if dt is None else dt
+        self.kept = 5 if dt is None else 4
+        self.t_last, self.dt = flat[9 * n:10 * n], flat[10 * n:] if dt is None else dt
 
     def _arrays(self):
         return self.r, self.v, self.a, self.t_last, self.dt
@@ -104,26 +103,23 @@ class _State:
             done += x.numel()
 
     @classmethod
-    def start(cls, ctx: Context, r0, v0, m, dt, kept=5):
-        """r0, v0 at time 0 with steps dt, checkpoints of the first `kept` arrays; zero
-        accelerations, which the prediction at time 0 reads before the first force gives
-        them."""
-        n, like = ctx.n, dict(dtype=torch.float64, device=ctx.device)
-        own = None  # the steps, where the checkpoints leave them out
-        if kept < 5:
-            own = torch.full((n,), dt, **like) if isinstance(dt, float) else dt.to(**like)
-        zero = torch.zeros((11 if own is None else 10) * n, **like)
-        st = cls(ctx, zero[:(6 + kept) * n], zero[9 * n:10 * n] if kept < 4 else None, own)
-        if own is None:
+    def start(cls, ctx: Context, r0, v0, m, dt, steps_change=False):
+        """r0, v0 at time 0 with steps dt, saved with the state if they change along the
+        way; zero accelerations, which the prediction at time 0 reads before the first
+        force gives them."""
+        n = ctx.n
+        flat = torch.zeros((10 + steps_change) * n, dtype=torch.float64, device=ctx.device)
+        st = cls(ctx, flat, None if steps_change else dt)
+        if steps_change:
             st.dt.copy_(dt.reshape(n))
         st.r.copy_(r0.reshape(3, n))
         st.v.copy_(v0.reshape(3, n))
         return st.bind(ctx, m.clone())
 
     @classmethod
-    def like(cls, ctx: Context, flat, m, t_last=None, dt=None):
+    def like(cls, ctx: Context, flat, m, dt=None):
         """A bound state of its own (its values come from a later restore)."""
-        return cls(ctx, torch.empty_like(flat), t_last, dt).bind(ctx, m)
+        return cls(ctx, torch.empty_like(flat), dt).bind(ctx, m)
 
 
 def _positions(ctx: Context, flat):
@@ -138,7 +134,8 @@ class TsbtsLeapfrog(torch.autograd.Function):
         n = ctx.n
         dev = ctx.device
         r0, v0, m = (x.detach().contiguous() for x in (r0, v0, m))
-        st = _State.start(ctx, r0, v0, m, float(h), kept=3)
+        st = _State.start(ctx, r0, v0, m,
+                          torch.full((n,), h, dtype=torch.float64, device=dev))
         every = ctx.idx(torch.arange(n, dtype=torch.int32))
         acc = torch.empty((3, n), dtype=torch.float64, device=dev)
         ctx.predict(0.0)
@@ -171,13 +168,12 @@ class TsbtsLeapfrog(torch.autograd.Function):
         g = z()
         mbar = torch.zeros(n, dtype=torch.float64, device=dev)
         acc = torch.empty((3, n), dtype=torch.float64, device=dev)
-        st = _State.like(ctx, fctx.checkpoints[0][1], m, torch.empty_like(mbar), fctx.dt)
+        st = _State.like(ctx, fctx.checkpoints[0][1], m, fctx.dt)
         for (s0, flat) in reversed(fctx.checkpoints):
             s1 = min(s0 + era, steps)
             # recompute the era from its checkpoint, keeping the positions of every step;
             # the last step's are its prediction, its force is not needed
             st.restore(flat)
-            st.t_last.fill_(s0 * h)
             pos = []
             for s in range(s0, s1 - 1):
                 _step(ctx, every, acc, s, h)
@@ -260,7 +256,8 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
         dev = ctx.device
         sched = BlockSchedule(ctx, dt, t_end)
         r0, v0, m = (x.detach().contiguous() for x in (r0, v0, m))
-        st = _State.start(ctx, r0, v0, m, torch.tensor(sched.dt), kept=4)
+        st = _State.start(ctx, r0, v0, m,
+                          torch.tensor(sched.dt, dtype=torch.float64, device=dev))
         every = sched.sets[-1]
         buf = torch.empty(3 * n, dtype=torch.float64, device=dev)
         ctx.predict(0.0)
@@ -294,7 +291,7 @@ class TsbtsBlockLeapfrog(torch.autograd.Function):
         buf = torch.empty(3 * n, dtype=torch.float64, device=dev)
         seeds = torch.empty(3 * n, dtype=torch.float64, device=dev)
         first = fctx.checkpoints[0][1]
-        st = _State.like(ctx, first, m, dt=fctx.dt)
+        st = _State.like(ctx, first, m, fctx.dt)
         for (s0, flat) in reversed(fctx.checkpoints):
             s1 = min(s0 + era, sched.K)
             st.restore(flat)
@@ -427,7 +424,7 @@ class TsbtsScheduleLeapfrog(torch.autograd.Function):
         n = ctx.n
         dev = ctx.device
         r0, v0, m = (x.detach().contiguous() for x in (r0, v0, m))
-        st = _State.start(ctx, r0, v0, m, sched.dt0)
+        st = _State.start(ctx, r0, v0, m, sched.dt0, steps_change=True)
         every = ctx.idx(torch.arange(n, dtype=torch.int32))
         buf = torch.empty(3 * n, dtype=torch.float64, device=dev)
         ctx.predict(0.0)

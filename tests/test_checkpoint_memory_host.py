@@ -1,6 +1,6 @@
 """What the checkpoints of a differentiated run hold (CPU stand-in context): positions,
-velocities and accelerations of a shared-step run (its times and steps are known), the
-particles' times too of a block run, their steps too of a run on a recorded schedule."""
+velocities, accelerations and times of a run whose steps stay the same, the steps too of a
+run on a recorded schedule."""
 import numpy as np
 import pytest
 import torch
@@ -26,7 +26,7 @@ def _run(kind):
     return [(0, s) for s in tsbts_schedule_leapfrog(*x, ctx, sched)[0].grad_fn.starts]
 
 
-@pytest.mark.parametrize("kind,values", [("shared", 9), ("block", 10), ("schedule", 11)])
+@pytest.mark.parametrize("kind,values", [("shared", 10), ("block", 10), ("schedule", 11)])
 def test_values_per_particle_of_a_checkpoint(kind, values):
     held = _run(kind)
     assert len(held) == 3
