@@ -12,7 +12,7 @@
 // half at the end): 11 instructions and 60 issue cycles per wave of pairs, 16 of them
 // the estimate.  Bound by vector ALU issue; sources staged in LDS (two broadcast reads of
 // 16 bytes per pair, 64 of 68 cycles of a CU's LDS) were as slow as the arithmetic.
-// N = 131072: 4.06 -> 3.60 ms.
+// N = 131072: 4.06 -> 3.60 ms.  (s from 5.6e-309, below which y^2 overflows: rsqrt_f64.)
 #include <algorithm>
 
 #include "internal.hpp"
@@ -24,14 +24,21 @@ constexpr int kTE = 256;
 constexpr int64_t kMaxEB = 8192;  // workgroups (and partials) of the pair kernel
 // With few tile pairs each is cut into parts of its sources, up to kMaxParts and about
 // kPartItems items: a serial chain of 256 pairs per lane would set the time (us, whole
-// tile pairs and parts: N = 1000 24.6, 7.6; 4096 25.0, 12.8; 8192 36.5, 27.0).
-constexpr int64_t kPartItems = 4096;
+// tile pairs and parts: N = 1000 24.6, 7.6; 4096 25.0, 12.8; 8192 36.5, 27.0).  Two parts pay
+// up to kPartItemsTwo items, whose last round of workgroups would be nearly empty otherwise
+// (N = 16384 76.1, 71.6; 18077 88.5, 83.2; 9000 in 8 parts instead of 4 30.1, 31.6; 22000 in
+// 2 instead of 1 117.1, 117.7).
+constexpr int64_t kPartItems = 4096, kPartItemsTwo = 6144;
 constexpr int kMaxPartBits = 3;
+}  // namespace
+
 int energy_part_bits(int64_t ntp) {
   int q = 0;
-  while (q < kMaxPartBits && (2 * ntp << q) <= kPartItems) ++q;
+  while (q < kMaxPartBits && (2 * ntp << q) <= (q == 0 ? kPartItemsTwo : kPartItems)) ++q;
   return q;
 }
+
+namespace {
 
 struct EnergyArgs {
   int64_t n;

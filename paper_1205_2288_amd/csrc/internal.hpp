@@ -127,7 +127,9 @@ __device__ __forceinline__ double rsq_f64_approx(double x) { return __builtin_am
 // 1/sqrt(s) in float64 from the hardware estimate y and its residual e = 1 - s y^2 (at most
 // 1.04e-7): y (1 + e/2 + 3 e^2/8), the next term below 1e-21.  Five operations where two
 // Newton steps take seven, and nearer (1 - s y^2 at most 3.8e-16 against 5.3e-16, mean
-// 7e-20 against 3e-17 over s = 2^-40 .. 2^40).
+// 7e-20 against 3e-17 over s = 2^-40 .. 2^40).  For s from 5.6e-309: below, y^2 overflows,
+// where the Newton steps still gave the root (separations below 7.5e-155 without softening,
+// whose accelerations overflow either way).
 __device__ __forceinline__ double rsqrt_f64(double s) {
   const double y = rsq_f64_approx(s);
   const double e = fma(-s, y * y, 1.0);
@@ -453,7 +455,9 @@ constexpr int kShareTiles = kShareMaxAct / 64;
 // instead of a second launch.  Block steps of 33 to 256 targets, in us (separate, fused):
 // float64 N = 256 (4 slices) 26.8, 24.5, N = 500 (8) 29.3, 26.1; mixed N = 1000 (4, the
 // criterion separate) 32.5, 32.1, with its 16 slices fused too 38.5; N = 4096 (16 and 64
-// fused) 32.4, 40: more slices wait longer for the last one than a launch takes.
+// fused) 32.4, 40: more slices wait longer for the last one than a launch takes.  So few are
+// N <= 512 in float64, N <= 2048 for the mixed force, and there N = 7681 to 8192 from 3841
+// targets too, whose units are 256 j-particles per wave.
 constexpr int kShareFuse = 8;
 constexpr int kChunkTiny = 16;
 struct ShareShape {
@@ -477,6 +481,8 @@ inline uint32_t *share_done(const tsbts_ctx *c, int which) {
 // The split of n_cols j-particles for n_targets (chunk 0: 64, or 16 for few).
 ShareShape share_split(int64_t n_targets, int64_t n_cols, int chunk);
 int64_t share_partials_reserve(const tsbts_ctx *c);
+// Parts of each of ntp tile pairs' sources in the energy, as a power of two (energy.hip).
+int energy_part_bits(int64_t ntp);
 int64_t gather_partials_reserve(const tsbts_ctx *c);
 // Whether a call on this stream may allocate: not while the stream is captured, nor when
 // that cannot be told (the legacy stream during another stream's capture).

@@ -27,7 +27,7 @@
 namespace tsbts {
 namespace {
 
-constexpr int kGroup = 16;     // targets of a wave
+constexpr int kGroup = 16;     // targets of a workgroup
 // Computed squares and bounds are off by a few float32 roundings: the distance is taken
 // smaller and the speed larger by far more than those.
 constexpr float kNear = 0.9999f, kFast = 1.0001f;

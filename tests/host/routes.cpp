@@ -70,3 +70,5 @@ int route_share(const tsbts_ctx *c, int k) {
 }
 
 extern "C" int route_first(const tsbts_ctx *c, int k) { return criterion_first(c, k) ? 1 : 0; }
+
+extern "C" int route_energy_bits(int64_t ntp) { return energy_part_bits(ntp); }

@@ -28,6 +28,7 @@ def routes(tmp_path_factory):
     r = ctypes.CDLL(out)
     r.route_ctx.restype = ctypes.c_void_p
     r.route_ctx.argtypes = [ctypes.c_int64, ctypes.c_int]
+    r.route_energy_bits.argtypes = [ctypes.c_int64]
     for name in ("route_force_rows", "route_step_rows"):
         getattr(r, name).argtypes = [ctypes.c_int, ctypes.c_int64, ctypes.c_int]
     for name in ("route_free", "route_step_done", "route_reserve"):
@@ -182,3 +183,12 @@ def test_native_step_takes_the_criterion_before_the_force(routes, make, precisio
     c = make(n, precision)
     assert all(routes.route_first(c, k) for k in (1, 32, 33, 300, 4095) if k <= n)
     assert not routes.route_first(c, 4096)
+
+
+def test_energy_cuts_tile_pairs_into_parts(routes):
+    # 8 parts of few tile pairs, 2 up to about N = 19800 (between one and one and a half
+    # rounds of workgroups uncut), none beyond
+    bits = {n: routes.route_energy_bits((t := (n + 255) // 256) * (t + 1) // 2)
+            for n in (1, 1000, 4096, 5633, 9000, 11500, 14871, 16384, 18077, 20000, 131072)}
+    assert bits == {1: 3, 1000: 3, 4096: 3, 5633: 3, 9000: 2, 11500: 1, 14871: 1, 16384: 1,
+                    18077: 1, 20000: 0, 131072: 0}
