@@ -99,6 +99,13 @@ __device__ __forceinline__ void finish(const ForceArgs &A, int q, int64_t g, dou
   if (A.correct) correct_target(A.corr, q, g, an, ts ? *ts : load_target(A.corr, g), vnew);
 }
 
+// Whether the softening is a vector operand: not in the float32 pairs with the potential and
+// without a Newton step, where its register costs more than its slower issue (21700 of N =
+// 74547 640 us as a vector, 620 as a scalar; without the potential 586, 608; with the Newton
+// step 728, 733).
+template <class F, int NEWTON, int POT>
+constexpr bool kVectorEps = sizeof(F) == 8 || NEWTON || !POT;
+
 template <class V, int NEWTON, int MASK, int POT, int IPL, class F>
 __device__ __forceinline__ void tile_loop(const typename V::J *sj, const typename V::I *I,
                                           const int *g, int64_t jbase, F eps2, F *fx, F *fy,
@@ -125,7 +132,8 @@ __global__ __launch_bounds__(kWG) void k_force(ForceArgs A) {
   const int jt0 = slice * A.plan.tiles_per_slice;
   const int jt1 = min(jt0 + A.plan.tiles_per_slice, A.n_jtiles);
   const int64_t P = A.npad;
-  const F eps2 = in_vector(sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2));
+  const F eps2s = sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2);
+  const F eps2 = kVectorEps<F, NEWTON, POT> ? in_vector(eps2s) : eps2s;
 
   typename V::I I[IPL];
   int q[IPL];
@@ -234,7 +242,8 @@ __global__ __launch_bounds__(kWG) void k_force_scalar(ForceArgs A) {
   if (slice >= A.plan.n_slices) return;
   const int jt0 = slice * A.plan.tiles_per_slice;
   const int jt1 = min(jt0 + A.plan.tiles_per_slice, A.n_jtiles);
-  const F eps2 = in_vector(sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2));
+  const F eps2s = sizeof(F) == 4 ? static_cast<F>(A.eps2f) : static_cast<F>(A.eps2);
+  const F eps2 = kVectorEps<F, NEWTON, POT> ? in_vector(eps2s) : eps2s;
   const int lane = static_cast<int>(threadIdx.x) & 63;
   const int w = SH == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q = SH == 1 ? itile * kWG + static_cast<int>(threadIdx.x) : itile * 64 + lane;
