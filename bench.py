@@ -70,16 +70,16 @@ FLOPS_ADJOINT_GATHER = 73.0  # fused all-active gather kernel: source 38 + targe
 # 16 hex digits) when the counters were taken; if they differ now, traffic is null.
 COUNTER_SCALE = {"fetch": 2.0, "write": 1.0}
 TRAFFIC_KIB = {
-    "k_force_sym": (134838.2, 363358.0,
+    "k_force_sym": (134822.0, 363360.0,
         ("force_sym.hip", "sym.hpp", "force_pair.hpp", "pair.hpp", "internal.hpp",
          "correct.hpp"),
-        "22d539811e6e2289"),
-    "k_bwd_sym": (210271.6, 396288.0,
+        "efdfe5dcdf66d0f3"),
+    "k_bwd_sym": (210224.2, 396288.0,
         ("backward_sym.hip", "sym.hpp", "pair.hpp", "internal.hpp"),
-        "1d5043e8a01cc2c9"),
-    "k_energy_pairs": (33877.6, 256.0,
+        "f8b7a5d7337bcc2c"),
+    "k_energy_pairs": (34123.2, 256.0,
         ("energy.hip", "internal.hpp"),
-        "7043070b8cca35d7"),
+        "6a80ebc4b7cb6e6c"),
 }
 
 
