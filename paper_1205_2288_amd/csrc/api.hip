@@ -537,7 +537,7 @@ int tsbts_timestep(tsbts_ctx *c, const int32_t *idx, int32_t n_act, double eta, 
   // whose buffers are there
   if (!cells_criterion_applies(c, n_act) || !cells_prepare(c, stream)) {
     if (int s = ensure_part(c, partial_elems_needed(c, n_act))) return s;
-    if (may_allocate(stream)) {
+    if ((criterion_sym_applies(c, n_act) || split_applies(c, n_act)) && may_allocate(stream)) {
       if (criterion_sym_applies(c, n_act)) {
         const int vb = c->precision == TSBTS_FP64 ? 8 : 4;
         if (int s = sym_prepare(c, 2, vb, vb))

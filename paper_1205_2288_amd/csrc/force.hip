@@ -865,9 +865,9 @@ int64_t share_partials_reserve(const tsbts_ctx *c) {
 }
 
 // The most that a force or criterion call of more than kSmallAct targets needs.  The split,
-// and with it the slices, changes where a workgroup's worth of targets is full (and where
-// another form begins, at such a number too), so the sizes there and one below are the
-// largest of their splits.  Rounding to whole units can leave a partial set more partials
+// and with it the slices, changes where a workgroup's worth of targets is full, so those
+// sizes are the largest of their splits, and the last ones of a form (below kShareMaxAct and
+// 8192 targets) of theirs.  Rounding to whole units can leave a partial set more partials
 // than all particles have (43008 of 50000 targets 16.9 million values, all of them 9.8).
 int64_t gather_partials_reserve(const tsbts_ctx *c) {
   int64_t need = 0;
@@ -875,12 +875,11 @@ int64_t gather_partials_reserve(const tsbts_ctx *c) {
     need = std::max(need, partial_elems_needed(c, static_cast<int>(std::min(k, c->n))));
   };
   take(c->n);
+  take(kShareMaxAct - 1);
+  take(8191);
   // (beyond two targets per lane in twice the workgroups aimed for nothing is split)
   const int64_t tiles = std::min<int64_t>((c->n + kWG - 1) / kWG, 4 * c->tune_blocks + 1);
-  for (int64_t t = 1; t <= tiles; ++t) {
-    take(t * kWG - 1);
-    take(t * kWG);
-  }
+  for (int64_t t = 1; t <= tiles; ++t) take(t * kWG);
   return need;
 }
 
